@@ -64,7 +64,8 @@ WORKLOADS = ("single_large", "single_small", "series", "sov", "sov_neumann", "di
 
 # the device sources of each workload's kernels
 # (with the host code that decides the launches: tiling, work lists, shapes)
-SOURCES_TILES = ("paper_1002_2469_amd/csrc/tdt_kernels.hip", "paper_1002_2469_amd/csrc/tdt_internal.h",
+SOURCES_TILES = ("paper_1002_2469_amd/csrc/tdt_kernels.hip", "paper_1002_2469_amd/csrc/tdt_short.hip",
+                 "paper_1002_2469_amd/csrc/tdt_device.h", "paper_1002_2469_amd/csrc/tdt_internal.h",
                  "paper_1002_2469_amd/csrc/tdt_api.cpp")
 SOURCES_POISSON = ("paper_1002_2469_amd/csrc/tdt_poisson.hip", "paper_1002_2469_amd/csrc/tdt_strided.hip",
                    "paper_1002_2469_amd/csrc/tdt_strided.h", "paper_1002_2469_amd/csrc/tdt_internal.h",

@@ -15,7 +15,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 LIB_PATH = os.path.join(_HERE, "libtdt.so")
 SOURCES = [os.path.join(_HERE, "csrc", "tdt_kernels.hip"), os.path.join(_HERE, "csrc", "tdt_api.cpp"),
-           os.path.join(_HERE, "csrc", "tdt_poisson.hip"), os.path.join(_HERE, "csrc", "tdt_strided.hip")]
+           os.path.join(_HERE, "csrc", "tdt_poisson.hip"), os.path.join(_HERE, "csrc", "tdt_strided.hip"),
+           os.path.join(_HERE, "csrc", "tdt_short.hip")]
 HEADER = os.path.join(_ROOT, "include", "tdt.h")
 
 # status codes (include/tdt.h)

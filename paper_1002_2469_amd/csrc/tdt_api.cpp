@@ -75,6 +75,13 @@ struct tdt_plan_s {
   float* dvec32[2] = {nullptr, nullptr};
   double* dtab64[2] = {nullptr, nullptr};
   float* dtab32[2] = {nullptr, nullptr};
+  // short systems (tdt_short.hip): which of them run there, and for
+  // quasi-Toeplitz systems the position table that starts from the corner
+  // row (qnt positions)
+  std::vector<char> short_ok[2];
+  int qnt = 0;
+  double* dqtab64[2] = {nullptr, nullptr};
+  float* dqtab32[2] = {nullptr, nullptr};
   double* dgreen[2] = {nullptr, nullptr};   // series with several tiles: [2][L]
   // rows of a tile the first pass reads from the head and the tail (0: all)
   int green_kf[2] = {0, 0}, green_kl[2] = {0, 0};
@@ -95,7 +102,8 @@ struct tdt_plan_s {
     int* grid = nullptr;    // systems with an interface pass across tiles
     int* whole = nullptr;   // systems solved whole by one workgroup each, by bins
     int* bins = nullptr;
-    int64_t n_p1 = 0, n_ends = 0, n_fin = 0, n_grid = 0, n_whole = 0, n_bins = 0;
+    int* shorts = nullptr;  // systems of at most kShortItemNT blocks
+    int64_t n_p1 = 0, n_ends = 0, n_fin = 0, n_grid = 0, n_whole = 0, n_bins = 0, n_short = 0;
   } lists[2];
   int64_t vslots = 0, vfslots = 0;
   // workspace
@@ -640,6 +648,8 @@ void destroy(tdt_plan_s* p) {
     (void)hipFree(p->dvec32[k]);
     (void)hipFree(p->dtab64[k]);
     (void)hipFree(p->dtab32[k]);
+    (void)hipFree(p->dqtab64[k]);
+    (void)hipFree(p->dqtab32[k]);
     (void)hipFree(p->dgreen[k]);
     (void)hipFree(p->dttab[k]);
     (void)hipFree(p->dgrow[k]);
@@ -657,13 +667,16 @@ void destroy(tdt_plan_s* p) {
     (void)hipFree(q.grid);
     (void)hipFree(q.whole);
     (void)hipFree(q.bins);
+    (void)hipFree(q.shorts);
   }
   (void)hipFree(p->iters);
   free_workspace(p);
   delete p;
 }
 
-// Work lists of a varlen plan.  Systems of at most sys_max_tiles tiles are
+// Work lists of a varlen plan.  Systems of at most kShortItemNT blocks take a
+// wavefront each (tdt_short.hip): a workgroup of the plan's shape would leave
+// three quarters of its lanes or more idle.  Systems of at most sys_max_tiles tiles are
 // solved whole by one workgroup each (largest first); the others go through
 // the three kernels: first pass over their tiles, interface pass, final pass
 // over their tiles in the reverse of the first pass's order (the most
@@ -671,10 +684,12 @@ void destroy(tdt_plan_s* p) {
 tdt_status_t build_lists(tdt_plan_s* p, int dir, int max_tiles) {
   tdt_plan_s::Lists& q = p->lists[dir];
   std::vector<int2> p1, fin;
-  std::vector<int> grid, whole_sys;
+  std::vector<int> grid, whole_sys, shorts;
   for (int64_t s : p->order) {
     const int nt = p->hsys[0][s].ntiles;
-    if (nt <= max_tiles) {
+    if (p->short_ok[dir][s]) {
+      shorts.push_back((int)s);
+    } else if (nt <= max_tiles) {
       whole_sys.push_back((int)s);
     } else {
       for (int t = 0; t < nt; ++t) p1.push_back(make_int2((int)s, t));
@@ -752,7 +767,9 @@ tdt_status_t build_lists(tdt_plan_s* p, int dir, int max_tiles) {
   (void)hipFree(q.grid);
   (void)hipFree(q.whole);
   (void)hipFree(q.bins);
+  (void)hipFree(q.shorts);
   q = tdt_plan_s::Lists{};
+  q.n_short = (int64_t)shorts.size();
   q.n_p1 = (int64_t)p1.size();
   q.n_ends = (int64_t)ends.size();
   q.n_fin = (int64_t)fin.size();
@@ -765,12 +782,82 @@ tdt_status_t build_lists(tdt_plan_s* p, int dir, int max_tiles) {
   if (st == TDT_OK) st = dev_upload(&q.grid, grid.data(), grid.size());
   if (st == TDT_OK) st = dev_upload(&q.whole, whole.data(), whole.size());
   if (st == TDT_OK) st = dev_upload(&q.bins, bins.data(), bins.size());
+  if (st == TDT_OK) st = dev_upload(&q.shorts, shorts.data(), shorts.size());
   return st;
 }
 
 tdt_status_t build_varlen_lists(tdt_plan_s* p) {
   const tdt_status_t st = build_lists(p, 0, p->sys_max_tiles);
   return st == TDT_OK ? build_lists(p, 1, std::min(p->sys_max_tiles, 1)) : st;
+}
+
+// The position table of a quasi-Toeplitz system of one tile for the short
+// path: beta_{m-1} and 1/(1 - phi_first beta_{m-1}) of its blocks with the
+// elimination started from the first corner row (beta_{-1} = -t_1/(t_0+psi),
+// where the tiles' table starts from 0), then the closing pivot of the last
+// corner row and the two corner diagonal entries.  False if a pivot vanishes
+// (the system then goes through the interface pass).
+bool corner_table(const SysDesc& D, double psi, double chi, int NT, double* t64, float* t32) {
+  const int nb = (int)((D.n + tdt::kShortB - 1) / tdt::kShortB);
+  ld tail[4] = {D.blk[0], D.blk[1], D.blk[2], D.blk[3]};
+  const int bt = (int)((D.n - 1) % tdt::kShortB) + 1;
+  if (bt < tdt::kShortB && !segment_ends(D.a, D.b, D.c, bt, tail)) return false;
+  ld beta = D.qc[1];
+  for (int m = 0; m < nb; ++m) {
+    ld e[4];
+    for (int k = 0; k < 4; ++k) e[k] = m + 1 < nb ? (ld)D.blk[k] : tail[k];
+    const ld den = 1.0L - e[0] * beta;
+    if (!(std::fabs((double)den) > 1e-13)) return false;
+    const ld iD = 1.0L / den;
+    t64[m] = (double)beta;
+    t64[NT + m] = (double)iD;
+    beta = e[3] + e[1] * e[2] * beta * iD;
+    if (!std::isfinite((double)beta)) return false;
+  }
+  const ld den = 1.0L - (ld)D.qc[3] * beta;
+  if (!(std::fabs((double)den) > 1e-13)) return false;
+  double* q = t64 + 2 * NT;
+  q[tdt::kQTabClose] = (double)(1.0L / den);
+  q[tdt::kQTabD0] = (double)((ld)D.b + psi);
+  q[tdt::kQTabD1] = (double)((ld)D.b + chi);
+  for (int k = 0; k < 2 * NT + tdt::kQTabN; ++k) t32[k] = (float)t64[k];
+  return true;
+}
+
+// Which systems take the short path: those of one tile of 16-row blocks; in a
+// varlen plan those that fit one wavefront, if they are all of the batch or
+// at least four per compute unit.  Next to longer systems the short ones are
+// a launch of their own, about 5 us; in the other kernels a short system costs
+// about 14 ns of the whole device at 512 lanes and 5 ns at 256 (the 512 short
+// ones of the 2048-system separation-of-variables batch: 94.5 us together
+// with the others, 99.6 us in a launch of their own).
+tdt_status_t mark_short(tdt_plan_s* p, int dir) {
+  const size_t S = p->hsys[dir].size();
+  std::vector<char>& ok = p->short_ok[dir];
+  ok.assign(S, 0);
+  if (p->B != tdt::kShortB) return TDT_OK;
+  size_t count = 0;
+  for (size_t s = 0; s < S; ++s) {
+    ok[s] = p->hsys[dir][s].ntiles == 1 &&
+            (!p->varlen || p->in_sizes[s] <= (int64_t)tdt::kShortItemNT * tdt::kShortB);
+    count += ok[s];
+  }
+  if (count == 0 || (count < S && count < 4 * (size_t)tdt::device_cus())) {
+    ok.assign(S, 0);
+    return TDT_OK;
+  }
+  if (!p->quasi) return TDT_OK;
+  p->qnt = p->varlen ? tdt::kShortItemNT : p->NT;
+  const size_t pitch = (size_t)tdt::kTabN * p->qnt + tdt::kQTabN;
+  std::vector<double> q64(S * pitch, 0.0);
+  std::vector<float> q32(S * pitch, 0.0f);
+  for (size_t s = 0; s < S; ++s)
+    if (ok[s])
+      ok[s] = corner_table(p->hsys[dir][s], p->in_psi[s], p->in_chi[s], p->qnt,
+                           q64.data() + s * pitch, q32.data() + s * pitch);
+  tdt_status_t st = dev_upload(&p->dqtab64[dir], q64.data(), q64.size());
+  if (st == TDT_OK) st = dev_upload(&p->dqtab32[dir], q32.data(), q32.size());
+  return st;
 }
 
 // Build both descriptor sets (T and T^T) and upload everything.  sizes and
@@ -819,6 +906,8 @@ tdt_status_t finish_plan(tdt_plan_s* p, const std::vector<double>& tm1,
         }
       }
     }
+    const tdt_status_t sq = mark_short(p, dir);
+    if (sq != TDT_OK) return sq;
     // varlen bookkeeping: adjoint partial-sum slots, one per tile and one
     // per corner row
     int64_t fs = 0;
@@ -1243,6 +1332,40 @@ int64_t series_fslots(const tdt_plan_s* p, int64_t M) {
   return M * p->hsys[0][0].ntiles + (p->quasi ? 2 * M : 0);
 }
 
+// How a series of short systems (nb blocks each) is dealt to workgroups:
+// lanes per workgroup and systems per workgroup (0: by the tile kernels).
+// The narrowest workgroup that keeps at least 85 % as many lanes at work as
+// the best width does: narrow workgroups wait for fewer wavefronts and need
+// no LDS level (64 lanes), wider ones waste fewer lanes on system sizes that
+// do not divide them.
+void short_runs(const tdt_plan_s* p, int dir, int64_t M, int& nt, int& g, int64_t& runs) {
+  nt = g = 0;
+  runs = 0;
+  if (p->varlen || p->general || p->strided || !p->short_ok[dir][0]) return;
+  const int nb = (int)((p->hsys[dir][0].n + tdt::kShortB - 1) / tdt::kShortB);
+  // systems a workgroup of w lanes holds: its lanes' blocks, and its rows
+  // (a quasi-Toeplitz system's two corner rows lie outside its blocks)
+  auto fits = [&](int w) {
+    return (int)std::min<int64_t>(w / nb, (int64_t)w * tdt::kShortB / p->N);
+  };
+  auto used = [&](int w) { return (double)(fits(w) * nb) / w; };
+  double best = 0.0;
+  for (int w = 64; w <= p->NT; w *= 2) best = std::max(best, used(w));
+  for (int w = 64; w <= p->NT && best > 0.0; w *= 2)
+    if (used(w) >= 0.85 * best) {
+      nt = w;
+      break;
+    }
+  if (nt == 0) return;
+  g = fits(nt);
+  // a whole workgroup of the plan's shape per system: the tile kernels do that
+  if (g == 1 && nt == p->NT && !p->quasi) {
+    nt = g = 0;
+    return;
+  }
+  runs = (M + g - 1) / g;
+}
+
 // The launch set of a solve (everything but the workspace and the profile
 // events) and the tile slots / adjoint partial-sum slots it needs.
 tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::LaunchSet& L,
@@ -1272,6 +1395,9 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
   L.gen_blk = p->dgblk[dir];
   L.gen_tK = p->dgtK[dir];
   L.gen_M = M;
+  L.qtab64 = p->dqtab64[dir];
+  L.qtab32 = p->dqtab32[dir];
+  L.qnt = p->qnt;
   if (p->general) {
     const SysDesc& D0 = p->hsys[0][0];
     const int64_t nt = D0.ntiles;
@@ -1321,6 +1447,8 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     L.ends_items = q.n_ends > 0 ? q.ends : nullptr;
     L.n_ends = q.n_ends;
     L.gpack = p->dgpack[dir];
+    L.short_items = q.shorts;
+    L.n_short = q.n_short;
     slots = p->vslots;
     fslots = adjoint ? p->vfslots : 0;
     L.corner0 = 0;
@@ -1344,6 +1472,8 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     L.n_p1 = itf ? M * nt : 0;
     L.n_grid = itf ? M : 0;
     L.n_fin = M * nt;
+    short_runs(p, dir, M, L.short_nt, L.short_g, L.short_runs);
+    L.short_M = M;
     slots = itf ? M * D0.tslots : 0;
     fslots = adjoint ? series_fslots(p, M) : 0;
     L.corner0 = M * nt;
@@ -1959,7 +2089,10 @@ tdt_status_t tdt_solve_backward(tdt_plan_t p, const void* gX, const void* X, voi
   tdt_status_t st = run(p, 1, gX, gF, X, M, stream);
   if (st != TDT_OK) return st;
   if (d_gt) {
-    const int64_t nparts = p->varlen ? p->vfslots : series_fslots(p, M);
+    int nt, g;
+    int64_t runs;
+    short_runs(p, 1, M, nt, g, runs);   // one partial per run of short systems
+    const int64_t nparts = p->varlen ? p->vfslots : (g > 0 ? runs : series_fslots(p, M));
     if (tdt::launch_gt_reduce(p->gpart, p->dsys[1], p->S, nparts, p->varlen ? 1 : 0,
                               p->quasi ? tdt::kGradN : 3, d_gt, stream) != hipSuccess)
       return TDT_ERR_HIP;

@@ -107,6 +107,16 @@ enum { kVecIU = 0, kVecCP = 1, kVecPHI = 2, kVecCHI = 3, kVecAIU = 4, kVecN = 5 
 enum { kGenIU = 0, kGenAIU = 1, kGenCP = 2, kGenRowN = 3 };
 enum { kGenPF = 0, kGenPL = 1, kGenCF = 2, kGenBP = 3, kGenID = 4, kGenBlkN = 5 };
 
+// Short systems (tdt_short.hip): blocks of kShortB rows, as the plan's; a
+// varlen plan gives each such system (up to kShortItemNT blocks) a workgroup
+// of kShortItemNT lanes of its own.  Quasi-Toeplitz plans hold a second
+// per-position table for them, whose elimination starts from the first
+// corner row; after its positions: 1/(1 - qc[3] beta_last) and the two corner
+// diagonal entries.
+constexpr int kShortB = 16;
+constexpr int kShortItemNT = 64;
+enum { kQTabClose = 0, kQTabD0 = 1, kQTabD1 = 2, kQTabN = 4 };
+
 // Everything one solve launch sequence needs (device pointers).
 struct LaunchSet {
   const SysDesc* sys;
@@ -143,6 +153,16 @@ struct LaunchSet {
   double* ghost;
   double* gscr;
   double* gpart;
+  // short systems: a series of short_M right-hand sides in short_runs runs
+  // of short_g systems, one per workgroup of short_nt lanes (short_g = 0: none),
+  // or the n_short systems short_items of a varlen plan
+  int short_nt, short_g;
+  int64_t short_runs, short_M;
+  const int* short_items;
+  int64_t n_short;
+  const double* qtab64;   // quasi-Toeplitz: [ncidx][2 qnt + kQTabN]
+  const float* qtab32;
+  int qnt;
   int64_t corner0;        // series, quasi-Toeplitz: first corner t-gradient slot
   int quasi;              // the plan's systems are quasi-Toeplitz
   // general (per-row) matrix, series plans: per-row LU and per-block constants
@@ -171,6 +191,10 @@ int series_solve_prepare(tdt_plan_s* p, const void* F, void* X, int64_t M, Launc
 // dtype: 0 double, 1 float, 2 float sweeps with double refinement.
 hipError_t launch_solve(int dtype, bool bwd, const LaunchSet& L, const void* F, void* X,
                         const void* Xfwd, hipStream_t st);
+// The short systems of a launch set.
+hipError_t launch_short(int dtype, bool bwd, const LaunchSet& L, const void* F, void* X,
+                        const void* Xfwd, hipStream_t st);
+int device_cus();
 // Workgroups of the whole-system kernel that are resident at once (the
 // plan spreads its systems over this many lists).
 int sys_wg_capacity(int shape, int dtype, int wg_per_cu, int quasi);
