@@ -1993,38 +1993,62 @@ __global__ __launch_bounds__(NTG) void k_grid_affine_lean(GridArgs A) {
   }
 }
 
-// Deterministic second stage of the t-gradient sums: series plans sum all
-// partials (one workgroup, fixed tree); varlen plans sum each system's tiles
-// in order (one thread per system).  A partial slot holds ncomp values: 3
-// (t_-1, t_0, t_1), or 5 with (psi, chi) for quasi-Toeplitz plans.
-__global__ __launch_bounds__(kGridNT) void k_gt_reduce(const double* __restrict__ gpart,
-                                                   const SysDesc* __restrict__ sys,
-                                                   int64_t nsys, int64_t nparts, int varlen,
-                                                   int ncomp, double* __restrict__ gt) {
-  if (varlen) {
-    const int64_t s = (int64_t)blockIdx.x * kGridNT + threadIdx.x;
-    if (s >= nsys) return;
-    const int64_t f0 = sys[s].fslot0;
-    // the system's tiles, then its two corner rows (quasi-Toeplitz)
-    const int nf = sys[s].ntiles + (sys[s].quasi ? 2 : 0);
-    double acc[kGradN] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int t = 0; t < nf; ++t)
-      for (int c = 0; c < ncomp; ++c) acc[c] += gpart[ncomp * (f0 + t) + c];
-    for (int c = 0; c < ncomp; ++c) gt[ncomp * s + c] = acc[c];
-    return;
+// Deterministic second stage of the t-gradient sums.  A partial slot holds
+// ncomp values: 3 (t_-1, t_0, t_1), or 5 with (psi, chi) for quasi-Toeplitz
+// plans.  Bound by the latency of its loads (a few hundred kilobytes at
+// most), so that every thread keeps eight of them in flight.  Varlen plans:
+// one thread per system and component adds the system's slots in order, in
+// workgroups of one wavefront over the whole device (one thread per system
+// in workgroups of 512 took GTV0 us on 1000 quasi-Toeplitz systems, now GTV1
+// us).  Series plans: one workgroup adds all slots, thread k the slots k,
+// k + 512, ..., then a fixed tree.
+constexpr int kGtItemNT = 64;
+__device__ __forceinline__ double sum_slots(const double* p, int64_t stride, int64_t n) {
+  double acc = 0.0;
+  int64_t t = 0;
+  for (; t + 8 <= n; t += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = p[(t + u) * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += v[u];
   }
+  double v[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) v[u] = t + u < n ? p[(t + u) * stride] : 0.0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (t + u < n) acc += v[u];
+  return acc;
+}
+
+__global__ __launch_bounds__(kGtItemNT) void k_gt_reduce_items(const double* __restrict__ gpart,
+                                                               const SysDesc* __restrict__ sys,
+                                                               int64_t nsys, int ncomp,
+                                                               double* __restrict__ gt) {
+  const int64_t id = (int64_t)blockIdx.x * kGtItemNT + threadIdx.x;
+  if (id >= nsys * ncomp) return;
+  const int64_t s = id / ncomp, c = id - s * ncomp;
+  // the system's tiles, then its two corner rows (quasi-Toeplitz)
+  const int nf = sys[s].ntiles + (sys[s].quasi ? 2 : 0);
+  gt[id] = sum_slots(gpart + ncomp * (int64_t)sys[s].fslot0 + c, ncomp, nf);
+}
+
+__global__ __launch_bounds__(kGridNT) void k_gt_reduce(const double* __restrict__ gpart,
+                                                   int64_t nparts, int ncomp,
+                                                   double* __restrict__ gt) {
   __shared__ double red[kGridNT][kGradN];
-  double acc[kGradN] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int64_t k = threadIdx.x; k < nparts; k += kGridNT)
-    for (int c = 0; c < ncomp; ++c) acc[c] += gpart[ncomp * k + c];
-  for (int c = 0; c < kGradN; ++c) red[threadIdx.x][c] = acc[c];
+  const int tid = threadIdx.x;
+  const int64_t n = tid < nparts ? (nparts - tid + kGridNT - 1) / kGridNT : 0;
+  for (int c = 0; c < ncomp; ++c)
+    red[tid][c] = sum_slots(gpart + ncomp * (int64_t)tid + c, (int64_t)ncomp * kGridNT, n);
   __syncthreads();
   for (int h = kGridNT / 2; h >= 1; h >>= 1) {
-    if ((int)threadIdx.x < h)
-      for (int c = 0; c < kGradN; ++c) red[threadIdx.x][c] += red[threadIdx.x + h][c];
+    if (tid < h)
+      for (int c = 0; c < ncomp; ++c) red[tid][c] += red[tid + h][c];
     __syncthreads();
   }
-  if (threadIdx.x == 0)
+  if (tid == 0)
     for (int c = 0; c < ncomp; ++c) gt[c] = red[0][c];
 }
 
@@ -2802,9 +2826,12 @@ int sys_wg_capacity(int shape, int dtype, int wg_per_cu, int quasi) {
 
 hipError_t launch_gt_reduce(const double* gpart, const SysDesc* sys, int64_t nsys,
                             int64_t nparts, int varlen, int ncomp, double* gt, hipStream_t st) {
-  const unsigned grid = varlen ? (unsigned)((nsys + kGridNT - 1) / kGridNT) : 1u;
-  hipLaunchKernelGGL(k_gt_reduce, dim3(grid), dim3(kGridNT), 0, st, gpart, sys, nsys, nparts,
-                     varlen, ncomp, gt);
+  if (varlen)
+    hipLaunchKernelGGL(k_gt_reduce_items,
+                       dim3((unsigned)((nsys * ncomp + kGtItemNT - 1) / kGtItemNT)),
+                       dim3(kGtItemNT), 0, st, gpart, sys, nsys, ncomp, gt);
+  else
+    hipLaunchKernelGGL(k_gt_reduce, dim3(1), dim3(kGridNT), 0, st, gpart, nparts, ncomp, gt);
   return hipGetLastError();
 }
 
