@@ -189,12 +189,15 @@ tdt_status_t tdt_solve_strided(tdt_plan_t plan, const double *F, double *X, int6
  * on Nx x Ny interior points with u = 0 on the boundary.  A sine transform
  * along x (a real FFT of length Nx+1 of each folded row, then a prefix sum
  * for the odd coefficients: in one kernel when Nx+1 is a power of two from
- * 128 to 8192, through hipFFT otherwise) leaves one tridiagonal Toeplitz
+ * 128 to 8192, or any number up to 8192 whose prime factors are at most 13,
+ * through hipFFT otherwise) leaves one tridiagonal Toeplitz
  * system per mode k along y, t_+-1 = -1,
  * t_0 = 2 + hy^2 (4/hx^2) sin^2(pi k / (2 (Nx+1))); the inverse transform
- * gives U.  With the one-kernel transform and TDT_F64, the mode systems are
+ * gives U.  With the one-kernel transform and TDT_F64 (and, unless Nx+1 is a
+ * power of two, Nx >= 64 and Ny <= 1024), the mode systems are
  * solved in place in the transformed rows by a strided plan (system k is
- * column k; rows padded to ldw = 16 ceil(Nx/16) + 16 doubles): 2 row
+ * column k; rows padded to ldw = 16 ceil(Nx/16) + 16 doubles, 16 more where
+ * that is a multiple of 256): 2 row
  * transforms and the strided solve, no transposes; the workspace is Ny ldw
  * doubles plus the strided plan's 4 Nx ceil(Ny/512) when Ny > 1024.
  * Otherwise (TDT_F32_REFINE, or the hipFFT path) the transformed rows are
@@ -220,7 +223,11 @@ tdt_status_t tdt_poisson2d_solve(tdt_poisson_t p, const double *F, double *U,
                                  hipStream_t stream);
 /* The handle's line plan (owned by the handle), e.g. to set its options or
  * autotune it: a varlen plan, or the strided plan of the in-place path
- * (which takes no options). */
+ * (which takes no options).  Where Nx+1 is not a power of two, asking for it
+ * moves an in-place handle to mode-major order and a varlen plan, for this
+ * and every later solve (blocking; TDT_ERR_OOM and the handle unchanged if
+ * its buffers cannot be had): not while a solve may run or is being
+ * captured. */
 tdt_status_t tdt_poisson2d_line_plan(tdt_poisson_t p, tdt_plan_t *line);
 /* HIP events around the forward transform (with the transpose to mode-major
  * order on that path), the line solve and the inverse transform of every
@@ -246,7 +253,16 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p);
  * directions' operators; J_k is the smallest count whose error bound for a
  * full cycle, d_J^2 with d_J = prod_j (w_j - a)/(w_j + a), is <= eps, so the
  * 2-norm error of the result relative to the exact discrete solution is at
- * most eps (plus rounding).  J_k falls as k grows.  1 <= Ny, Nz <= 2^24
+ * most eps (plus rounding).  J_k falls as k grows.  Where Nx+1 has a
+ * one-kernel transform and Ny+1 and Nz+1 are at most 1024 with prime factors
+ * at most 13, the iterate is evaluated in closed form instead: both
+ * directions' operators commute and are diagonal in the sine basis of the
+ * plane, where the J_k steps from 0 leave
+ *   v = (1 - prod_j r_j(ly + mu_k/2) r_j(lz + mu_k/2)) fhat / (ly + lz + mu_k),
+ *   r_j(x) = (w_j - x) / (w_j + x),
+ * at eigenvalues ly, lz of A_y and A_z: sine transforms along y and z (in one
+ * pass each) around that factor.  The same iterate up to rounding.
+ * 1 <= Ny, Nz <= 2^24
  * (lines of more than 1024 points are solved in tiles of 512, as by
  * tdt_solve_strided), 640 Nxp Ny < 2^31 with Nxp = 16 ceil(Nx/16) + 16 on
  * the fused path, Nx otherwise (31-bit byte offsets of the z lines),
@@ -255,8 +271,9 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p);
  * mode and iteration, about twice that for tiled lines), for tiled lines
  * 4 Nx max(Nz ceil(Ny/512), Ny ceil(Nz/512)) doubles, and
  * 2 (16 ceil(Nx/16) + 16) Ny Nz doubles of workspace when
- * Nx+1 is a power of two from 128 to 8192 (the fused row transform; rows
- * padded to cache lines), else the FFT plan and (2 Nx + 3) Ny Nz doubles
+ * Nx+1 has a one-kernel transform (rows padded to cache lines; half of that,
+ * and two factors per mode and line eigenvalue instead of the per-iteration
+ * tables, in closed form), else the FFT plan and (2 Nx + 3) Ny Nz doubles
  * (allocated here, blocking).  Errors: bad sizes, spacings or eps ->
  * TDT_ERR_INVALID_ARG; allocation -> TDT_ERR_OOM; FFT plan -> TDT_ERR_HIP. */
 typedef struct tdt_poisson3d_s *tdt_poisson3d_t;

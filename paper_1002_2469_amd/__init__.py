@@ -407,10 +407,10 @@ class Poisson2D:
     """2D Poisson solve by separation of variables (Sec. 3.2): the five-point
     system on Nx x Ny interior points with zero boundary values, F and U
     [Ny][Nx] float64 on the device.  Sine transforms along x (one fused
-    kernel when Nx + 1 is a power of two from 128 to 8192, hipFFT
+    kernel when Nx + 1 is at most 8192 with prime factors at most 13, hipFFT
     otherwise), one Toeplitz line system per mode along y (in float64 with
-    the fused transform, a strided plan solving the modes in place in the
-    transformed rows; otherwise a varlen plan of dtype 'f64' or
+    the fused transform, mostly a strided plan solving the modes in place in
+    the transformed rows; otherwise a varlen plan of dtype 'f64' or
     'f32_refine' after a transpose), inverse transform."""
 
     def __init__(self, nx: int, ny: int, hx: float, hy: float, dtype: str = "f64"):
@@ -486,9 +486,11 @@ class Poisson2D:
 class Poisson3D:
     """3D Poisson solve of Sec. 3.5: the seven-point system on Nx x Ny x Nz
     interior points with zero boundary values, F and U [Nz][Ny][Nx] float64
-    on the device.  Sine transform along x (hipFFT), Peaceman-Rachford ADI
-    on every mode's (y, z) plane with the optimal parameters (strided line
-    solves along y and z), inverse transform.  eps bounds the ADI error
+    on the device.  Sine transform along x, Peaceman-Rachford ADI on every
+    mode's (y, z) plane with the optimal parameters (strided line solves
+    along y and z, or the same iterate in closed form through sine transforms
+    along y and z where Ny + 1 and Nz + 1 have small factors), inverse
+    transform.  eps bounds the ADI error
     relative to the exact discrete solution (2-norm)."""
 
     def __init__(self, nx: int, ny: int, nz: int, hx: float, hy: float, hz: float,
