@@ -148,7 +148,9 @@ tdt_status_t tdt_plan_general_create(int64_t N, const double *h_a, const double 
  * workgroup, and the blocks are corrected in registers.  A system of more
  * than 1024 rows is cut into tiles of 512 rows (the last one shorter), each
  * such a column: a first pass keeps the end values of every tile's solution
- * with zero outside values, one thread per system eliminates the tiles'
+ * with zero outside values (from the few rows near the tile's ends that
+ * matter where dominance lets the inverse's entries decay, Sec. 3.4, see
+ * tdt_green_support), one thread per system eliminates the tiles'
  * interface values (the recurrences of eq. (15) over the tiles), and a
  * second pass re-solves every tile with its two outside values.  The plan
  * holds per class the block LU, the blocks' end values and the interface
@@ -176,9 +178,10 @@ tdt_status_t tdt_plan_strided_create(int64_t N, int64_t P, const double *h_tm1,
  * N <= 1024: no workspace.  Longer N: the plan's workspace holds
  * 4 nb M ceil(N/512) doubles, allocated on first use or by
  * tdt_plan_reserve(plan, nb*M); a solve that needs more while its stream is
- * being captured returns TDT_ERR_CAPTURE.  Five launches then (two per pass,
- * the full tiles and the last one, and the interface), one otherwise; both
- * are capturable in a hipGraph.  Under tdt_plan_profile the kernel time is
+ * being captured returns TDT_ERR_CAPTURE.  Two launches then (one per pass;
+ * a third between them for more than 16 tiles or large batches, where the
+ * second pass does not eliminate the tiles' interface values itself), one
+ * otherwise; all are capturable in a hipGraph.  Under tdt_plan_profile the kernel time is
  * reported as the third value of tdt_plan_profile_read. */
 tdt_status_t tdt_solve_strided(tdt_plan_t plan, const double *F, double *X, int64_t M,
                                int64_t ld, int64_t nb, int64_t ldb, hipStream_t stream);
@@ -194,7 +197,7 @@ tdt_status_t tdt_solve_strided(tdt_plan_t plan, const double *F, double *X, int6
  * system per mode k along y, t_+-1 = -1,
  * t_0 = 2 + hy^2 (4/hx^2) sin^2(pi k / (2 (Nx+1))); the inverse transform
  * gives U.  With the one-kernel transform and TDT_F64 (and, unless Nx+1 is a
- * power of two, Nx >= 64 and Ny <= 1024), the mode systems are
+ * power of two, Nx >= 64 and Ny <= 2^24), the mode systems are
  * solved in place in the transformed rows by a strided plan (system k is
  * column k; rows padded to ldw = 16 ceil(Nx/16) + 16 doubles, 16 more where
  * that is a multiple of 256): 2 row

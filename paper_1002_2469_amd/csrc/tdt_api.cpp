@@ -64,6 +64,8 @@ struct tdt_plan_s {
   // full tile's tables, the last tile's and the end values one after
   // another at dstr
   int64_t sK = 1;
+  int* dsup = nullptr;      // its tiles' Green row supports (tdt::strided_sup), or null
+  double* dgeo = nullptr;
   bool varlen = false;
   tdt_dtype_t dtype = TDT_F64;
   int64_t N = 0;          // series: order of the system (with its corner rows)
@@ -658,6 +660,8 @@ void destroy(tdt_plan_s* p) {
     (void)hipFree(p->dggreen[k]);
   }
   (void)hipFree(p->dstr);
+  (void)hipFree(p->dsup);
+  (void)hipFree(p->dgeo);
   for (int k = 0; k < 2; ++k) {
     (void)hipFree(p->dgpack[k]);
     tdt_plan_s::Lists& q = p->lists[k];
@@ -1637,6 +1641,60 @@ int strided_tiled_tables(int64_t N, int64_t P, const double* tm1, const double* 
   }
   return TDT_OK;
 }
+void strided_sup(int64_t P, const double* tm1, const double* t0, const double* t1, int64_t NL,
+                 std::vector<int>& sup, std::vector<double>& geo) {
+  const int64_t G = (P + kStrGroup - 1) / kStrGroup;
+  sup.assign((size_t)(3 * G), 0);
+  geo.assign((size_t)(3 * P), 0.0);
+  bool any = false;
+  for (int64_t g = 0; g < G; ++g) {
+    int64_t kf = 1, kl = 1, Cmax = 0;
+    bool ok = true;
+    for (int64_t k = g * kStrGroup; k < std::min(P, (g + 1) * kStrGroup) && ok; ++k) {
+      // The pivots in closed form: u* the larger root of u^2 - t_0 u + t_-1 t_1,
+      // q = t_-1 t_1 / u*^2, u_i = u* (1 - q^(i+2)) / (1 - q^(i+1)), settled to
+      // long double rounding at C; umin as in green_support_bound is |u*|, or
+      // |t_0| = |u_0| where they alternate (q < 0)
+      const ld a = tm1[k], b = t0[k], c = t1[k];
+      const ld disc = b * b - 4.0L * a * c;
+      ok = disc > 0.0L && b != 0.0L;
+      if (!ok) break;
+      const ld us = 0.5L * (b + std::copysign(std::sqrt(disc), b)), q = a * c / (us * us);
+      const ld umin = q < 0.0L ? std::fabs(b) : std::fabs(us);
+      ok = std::fabs(q) < 1.0L;
+      if (!ok) break;
+      // (logarithms in double, rounded up and one more)
+      const int64_t C =
+          q == 0.0L ? 1 : (int64_t)std::ceil(-62.0 / std::log2((double)std::fabs(q))) + 2;
+      auto support = [&](ld t, int64_t& kk) {
+        const ld sr = std::fabs(t) / umin;
+        if (sr == 0.0L) return true;
+        if (!(sr < 1.0L)) return false;
+        const ld factor = std::fabs(us) / (umin * (1.0L - sr));
+        const double n =
+            std::ceil((-60.0 - std::log2((double)factor)) / std::log2((double)sr)) + 1.0;
+        if (!(n <= (double)kStrTile)) return false;
+        kk = std::max(kk, (int64_t)n);
+        return true;
+      };
+      ok = C < kStrTile && support(c, kf) && support(a, kl);
+      Cmax = std::max(Cmax, C);
+      geo[(size_t)k] = (double)(1.0L / us);
+      geo[(size_t)(P + k)] = (double)(-c / us);
+      geo[(size_t)(2 * P + k)] = (double)(-a / us);
+    }
+    // (reading more than half of the tile saves little over the sweep)
+    if (!ok || kf + kl > kStrTile / 2 || std::max(kf, kl) + Cmax > kStrTile) continue;
+    any = true;
+    sup[(size_t)(3 * g)] = (int)kf;
+    sup[(size_t)(3 * g + 1)] = (int)kl;
+    sup[(size_t)(3 * g + 2)] = NL >= std::max(kf, kl) + Cmax ? 1 : 0;
+  }
+  if (!any) {
+    sup.clear();
+    geo.clear();
+  }
+}
 }  // namespace tdt
 
 // ---------------------------------------------------------------------------
@@ -1954,6 +2012,13 @@ tdt_status_t tdt_plan_strided_create(int64_t N, int64_t P, const double* h_tm1,
   p->dominance = dom;
   p->kappa = 0.0;
   tdt_status_t s2 = dev_upload(&p->dstr, tab.data(), tab.size());
+  if (s2 == TDT_OK && K > 1) {
+    std::vector<int> sup;
+    std::vector<double> geo;
+    tdt::strided_sup(P, h_tm1, h_t0, h_t1, g.NL, sup, geo);
+    s2 = dev_upload(&p->dsup, sup.data(), sup.size());
+    if (s2 == TDT_OK) s2 = dev_upload(&p->dgeo, geo.data(), geo.size());
+  }
   if (s2 != TDT_OK) {
     destroy(p);
     return s2;
@@ -2015,7 +2080,8 @@ tdt_status_t tdt_solve_strided(tdt_plan_t p, const double* F, double* X, int64_t
   if (K == 1) {
     if (tdt::launch_strided(a, stream) != hipSuccess) return TDT_ERR_HIP;
   } else {
-    // pass 1 and pass 2 over the full tiles, then over the last one
+    a.sup = p->dsup;
+    a.geo = p->dgeo;
     if (tdt::launch_strided_tiled(a, tdt::strided_tiles(N, p->sP), p->dstr, p->summ, p->ghost,
                                   stream) != hipSuccess)
       return TDT_ERR_HIP;

@@ -788,9 +788,10 @@ tdt_status_t tdt_poisson2d_create(int64_t nx, int64_t ny, double hx, double hy,
   // in place in the transformed rows, as a strided batch (system k: column
   // k), with padded rows.  Otherwise transposes to and from mode-major order
   // around a varlen plan (also for short rows, whose padding would outweigh
-  // them, and for the mixed-radix sizes with more than one column's rows).
+  // them).  Measured in place and transposed: 199 x 3000 38.8 and 43.5 us,
+  // 999 x 1499 45 and 61, 4094 x 4000 276 and 402.
   p->strided = dtype == TDT_F64 &&
-               (p->fused || (p->any && nx >= 64 && ny <= tdt::kStrMaxChunks * tdt::kStrB));
+               (p->fused || (p->any && nx >= 64 && ny <= tdt::kStrMaxN));
   p->ldw = p->strided ? padded_row(nx) : n;
   tdt_status_t st =
       p->strided

@@ -4,6 +4,8 @@
 #include <stdint.h>
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 namespace tdt {
 
 // Strided batches: systems whose consecutive unknowns lie ld elements apart
@@ -54,7 +56,24 @@ struct StridedArgs {
   int64_t tiles, ldt, K, m0;
   double* Y;
   const double* Gh;
+  // A pass is one launch: workgroups with blockIdx.y < ysplit take the full
+  // tiles as above, the others the last tile of every batch, which lies
+  // off_last after the first and has its own order, blocks and tables.
+  int64_t ysplit, off_last, N_last;
+  int C_last;
+  const double *iu_last, *sc_last, *pos_last;
+  // Pass 2 with ends (K <= kStrInlineTiles): the workgroup eliminates the
+  // tiles' interface values of its systems itself, from Y.
+  const double* ends;
+  int xcd;                  // 1: contiguous stretches of the grid per XCD (launch_strided)
+  // Pass 1 with sup: the first and last unknown of a tile as dot products
+  // with the stretch of its Green rows that carries their mass (strided_sup).
+  const int* sup;           // [groups of 16 systems][3]
+  const double* geo;        // [3][P]
 };
+constexpr int kStrInlineTiles = 16;
+constexpr int64_t kStrInlineWork = 32768;
+constexpr int kStrGroup = 16;   // adjacent systems per workgroup of a tile
 hipError_t launch_strided(const StridedArgs& a, hipStream_t st);
 // The tiles' interface values of every system (one thread each), from the
 // tiles' end values Y: Gh receives every tile's left and right outside
@@ -70,6 +89,14 @@ struct StridedTiles {
   int C, CL;
   int64_t n_full, n_last, n_ends;
 };
+// The supports of the tiles' Green rows, per group of kStrGroup adjacent
+// classes (sup: head rows, tail rows, 1 if the last tile has them too; 0 rows:
+// the group's tiles are swept), and per class (geo: 1/u*, -t_1/u*, -t_-1/u*),
+// u* the value the elimination's pivots settle at: within the supports the
+// rows' entries are (-t_1)^j / u*^(j+1) from the first row's own end and
+// (-t_-1)^j / u*^(j+1) from the last one's.
+void strided_sup(int64_t P, const double* tm1, const double* t0, const double* t1, int64_t NL,
+                 std::vector<int>& sup, std::vector<double>& geo);
 StridedTiles strided_tiles(int64_t N, int64_t P);
 // The tables of a tiled system (host, long double; n_full + n_last + n_ends
 // doubles at out), with the tiles' interface pivots checked per class.
@@ -79,6 +106,7 @@ int strided_tiled_tables(int64_t N, int64_t P, const double* tm1, const double* 
 // ldb; tabs the tables above; Y and Gh hold nb K M 2 doubles each.
 hipError_t launch_strided_tiled(StridedArgs a, const StridedTiles& g, const double* tabs,
                                 double* Y, double* Gh, hipStream_t st);
+// (a.sup and a.geo, or null: pass 1 sweeps every tile)
 // Host tables of P classes (t_-1, t_0, t_1)[k] for systems of order N, in
 // long double: iu [kStrB][P], sc [kStrScalarN][P], pos [2][C][P].  Returns a
 // negative status on a singular class or bad arguments; *dominance is the
