@@ -426,8 +426,9 @@ tdt_status_t tdt_green_support(double t_m1, double t_0, double t_1, int64_t L, i
  * tiles' own inverses), rows4[2], rows4[3] the same for the adjoint (the
  * rows of T^T); 0, 0 when the pass reads whole tiles (the supports would
  * cover a quarter of the tile or more: weak dominance) or the plan has no
- * such pass (one tile, varlen or strided plans, or a general plan with a
- * ragged last tile).  Errors: null arguments -> TDT_ERR_INVALID_ARG. */
+ * such pass (one tile, varlen or strided plans).  A general plan with a
+ * ragged last tile reports 0, 0 as well (its pass reads the supports too,
+ * but not the same rows of every tile).  Errors: null arguments -> TDT_ERR_INVALID_ARG. */
 tdt_status_t tdt_plan_green_support(tdt_plan_t plan, int64_t *rows4);
 
 /* Host-only: the interface merge of two adjacent segments, in double, as the

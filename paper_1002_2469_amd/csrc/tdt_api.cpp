@@ -1175,9 +1175,8 @@ tdt_status_t build_general_dir(tdt_plan_s* p, int dir, double& dom, double& kap)
   std::vector<Tc> row((size_t)P * tdt::kGenRowN * L), blk((size_t)P * tdt::kGenBlkN * NT);
   std::vector<double> tK((size_t)P * 4);
   // the tiles' Green rows (the first pass's summaries are their dot
-  // products with the tile's F) and their supports: with several tiles,
-  // all of them full (no tail to mask), the first pass reads the widest
-  // supports over the tiles
+  // products with the tile's F) and their supports: with several tiles the
+  // first pass reads the widest supports over the tiles
   std::vector<double> green(P > 1 ? (size_t)P * 2 * L : 0);
   int64_t kfmax = 0, klmax = 0;
   for (int64_t t = 0; !green.empty() && t < P; ++t) {
@@ -1192,7 +1191,7 @@ tdt_status_t build_general_dir(tdt_plan_s* p, int dir, double& dom, double& kap)
     klmax = std::max(klmax, kl);
   }
   int gkf = 0, gkl = 0;
-  if (!green.empty() && N % L == 0) green_support_rounded(L, kfmax, klmax, gkf, gkl);
+  if (!green.empty()) green_support_rounded(L, kfmax, klmax, gkf, gkl);
   p->gen_kf[dir] = gkf;
   p->gen_kl[dir] = gkl;
   if (gkf > 0) {
@@ -1415,15 +1414,23 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     L.n_bins = L.n_sys = 0;
     L.n_beta = L.n_last = 0;
     L.nfull = 0;
-    // right-hand sides per item: up to 8 share one load of a tile's
-    // constants, as long as at least 4 items per compute unit remain
-    int R = (int)std::min<int64_t>(M, 8);
-    int dev = 0, cus = 0;
-    (void)hipGetDevice(&dev);
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1)
-      cus = 256;
-    while (R > 1 && nt * ((M + R - 1) / R) < 4 * (int64_t)cus) --R;
+    // Right-hand sides per item: up to 8 share one load of a tile's constants
+    // (about the traffic of two right-hand sides), and the rounds of resident
+    // workgroups over the items should be full.  The fewest rounds times
+    // (R + 2): 24 right-hand sides of 123 tiles in double take R = 6 (one
+    // round, final pass 46 us; R = 2, 50 us), 300 of 10 tiles 6 (45 against
+    // 52 us), 64 of 256 tiles 8.
+    const int64_t slots_g = std::max(1, tdt::general_slots(p->dtype == TDT_F32 ? 1 : 0));
+    int R = 1;
+    int64_t best = 0;
+    for (int r = 1; r <= 8 && r <= M; ++r) {
+      const int64_t items = nt * ((M + r - 1) / r);
+      const int64_t cost = (items + slots_g - 1) / slots_g * (r + 2);
+      if (best == 0 || cost <= best) {
+        best = cost;
+        R = r;
+      }
+    }
     L.gen_R = R;
     const int64_t groups = (M + R - 1) / R;
     L.n_p1 = nt > 1 ? groups * nt : 0;
@@ -2385,9 +2392,10 @@ tdt_status_t tdt_green_support(double t_m1, double t_0, double t_1, int64_t L, i
 
 tdt_status_t tdt_plan_green_support(tdt_plan_t p, int64_t* rows4) {
   if (!p || !rows4) return TDT_ERR_INVALID_ARG;
+  const bool whole = !p->general || p->N % p->L == 0;
   for (int dir = 0; dir < 2; ++dir) {
-    rows4[2 * dir] = p->general ? p->gen_kf[dir] : p->green_kf[dir];
-    rows4[2 * dir + 1] = p->general ? p->gen_kl[dir] : p->green_kl[dir];
+    rows4[2 * dir] = p->general ? (whole ? p->gen_kf[dir] : 0) : p->green_kf[dir];
+    rows4[2 * dir + 1] = p->general ? (whole ? p->gen_kl[dir] : 0) : p->green_kl[dir];
   }
   return TDT_OK;
 }

@@ -208,6 +208,7 @@ hipError_t launch_gt_reduce(const double* gpart, const SysDesc* sys, int64_t nsy
 // kShapes), and the entry gradients [3][n] from the adjoint solution gF and
 // the forward solution X ([M][n], floats if f32).
 constexpr int kGeneralShape = 1;
+int general_slots(int f32);   // workgroups of the general tile kernel resident at once
 hipError_t launch_general_grad(int f32, const void* gF, const void* X, int64_t n, int64_t M,
                                double* g, hipStream_t st);
 

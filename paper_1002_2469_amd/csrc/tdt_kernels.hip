@@ -1021,6 +1021,24 @@ __device__ __forceinline__ void beta_ends_item(const BetaEndsArgs<Tio>& A, int64
     gl = A.gstride ? gf + kf : gf + 2 * kTile - kl;
     head = A.F + S.off + m * S.stride + (int64_t)t * kTile;
     sl = tile_slot(S, m, t, false);
+    // a general plan's last tile is padded to a whole one with decoupled rows
+    // of right-hand side 0: the rows past the system are not read
+    const int64_t rest = S.n - (int64_t)t * kTile;
+    if (A.gstride && rest < kTile) {
+      double s1 = 0.0, s2 = 0.0;
+      for (int j = lane; part != 2 && j < kf; j += 64)
+        s1 += j < rest ? (double)head[j] * gf[j] : 0.0;
+      for (int j = lane; part != 1 && j < kl; j += 64)
+        s2 += kTile - kl + j < rest ? (double)head[kTile - kl + j] * gl[j] : 0.0;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) {
+        s1 += __shfl_xor(s1, d, 64);
+        s2 += __shfl_xor(s2, d, 64);
+      }
+      if (lane == 0 && part != 2) A.summ[2 * sl] = s1;
+      if (lane == 0 && part != 1) A.summ[2 * sl + 1] = s2;
+      return;
+    }
   }
   // the first row's head against the tile's first rows, the last row's
   // tail against its last rows
@@ -2248,12 +2266,14 @@ __global__ __launch_bounds__(SH::NT, SH::WAVES) void k_gtile(GenArgs<Tio, Tc> A)
 // Entry gradients of a general series plan after its adjoint solve:
 // g[0][i] = dL/da_i = -sum_m gF_{m,i} x_{m,i-1}, g[1][i] = dL/db_i =
 // -sum_m gF_{m,i} x_{m,i}, g[2][i] = dL/dc_i = -sum_m gF_{m,i} x_{m,i+1}
-// (0 for the unused a_0 and c_{n-1}); one thread per row, right-hand sides
-// in order (deterministic).
+// (0 for the unused a_0 and c_{n-1}), summed in a fixed order.  Bound by HBM
+// (both arrays read once).
+// k_ggrad_rows: one thread per row, right-hand sides in order; for double
+// rows enough to fill the device (2^18).
 template <typename Tio>
-__global__ __launch_bounds__(kGridNT) void k_ggrad(const Tio* __restrict__ gF,
-                                                const Tio* __restrict__ X, int64_t n, int64_t M,
-                                                double* __restrict__ g) {
+__global__ __launch_bounds__(kGridNT) void k_ggrad_rows(const Tio* __restrict__ gF,
+                                                        const Tio* __restrict__ X, int64_t n,
+                                                        int64_t M, double* __restrict__ g) {
   const int64_t i = (int64_t)blockIdx.x * kGridNT + threadIdx.x;
   if (i >= n) return;
   double sa = 0.0, sb = 0.0, sc = 0.0;
@@ -2268,6 +2288,68 @@ __global__ __launch_bounds__(kGridNT) void k_ggrad(const Tio* __restrict__ gF,
   g[i] = -sa;
   g[n + i] = -sb;
   g[2 * n + i] = -sc;
+}
+
+// The same with RB rows per workgroup, as few as fill the device, and SL
+// slices of the right-hand sides (slice k: k, k + SL, ..., U in flight), whose
+// sums meet in LDS and are added in order.  A thread per row leaves the
+// device idle on fewer rows, and float rows wait on its single loads: 4096
+// right-hand sides of 3000 rows 2983 us and 53 here, 300 of 40960 236 and 54,
+// 100 of 100000 84 and 47 (float, 64 of 2^20: 186 and 114 with U = 2); but 64
+// double ones of 2^20 221 and 248, 24 of 500009 44 and 48.
+constexpr int kGradNT = 1024;
+template <typename Tio, int U>
+__global__ __launch_bounds__(kGradNT) void k_ggrad(const Tio* __restrict__ gF,
+                                                   const Tio* __restrict__ X, int64_t n,
+                                                   int64_t M, int RB, int SL,
+                                                   double* __restrict__ g) {
+  __shared__ double red[3][kGradNT];
+  const int tid = threadIdx.x, r = tid % RB, k0 = tid / RB;
+  const int64_t i = (int64_t)blockIdx.x * RB + r;
+  const bool in = i < n, lf = in && i > 0, rt = i + 1 < n;
+  // the row's own and neighbouring elements (itself where there is none)
+  const int64_t ic = in ? i : 0, il = lf ? i - 1 : ic, ir = rt ? i + 1 : ic;
+  double sa = 0.0, sb = 0.0, sc = 0.0;
+  const Tio* gp = gF + k0 * n;
+  const Tio* xp = X + k0 * n;
+  const int64_t step = SL * n;
+  auto add = [&](double gv, double xl, double xc, double xr) {
+    sb += gv * xc;
+    sa += lf ? gv * xl : 0.0;
+    sc += rt ? gv * xr : 0.0;
+  };
+  int64_t m = k0;
+  if constexpr (U > 1) {
+    for (; m + (U - 1) * (int64_t)SL < M; m += U * SL) {
+      Tio gv[U], xl[U], xc[U], xr[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        gv[u] = gp[ic];
+        xl[u] = xp[il];
+        xc[u] = xp[ic];
+        xr[u] = xp[ir];
+        gp += step;
+        xp += step;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) add(gv[u], xl[u], xc[u], xr[u]);
+    }
+  }
+#pragma unroll 1
+  for (; m < M; m += SL, gp += step, xp += step) add(gp[ic], xp[il], xp[ic], xp[ir]);
+  red[0][tid] = sa;
+  red[1][tid] = sb;
+  red[2][tid] = sc;
+  __syncthreads();
+  // component c of a row: the slices in order
+  for (int e = tid; e < 3 * RB; e += RB * SL) {
+    const int c = e / RB, row = e - c * RB;
+    const int64_t io = (int64_t)blockIdx.x * RB + row;
+    if (io >= n) continue;
+    double s = 0.0;
+    for (int k = 0; k < SL; ++k) s += red[c][k * RB + row];
+    g[c * n + io] = -s;
+  }
 }
 }  // namespace tdt
 
@@ -2779,15 +2861,38 @@ static hipError_t run_general(const LaunchSet& L, const void* F, void* X, hipStr
   return hipGetLastError();
 }
 
+int general_slots(int f32) {
+  using SH = Shape<kShapes[kGeneralShape].B, kShapes[kGeneralShape].NT,
+                   kShapes[kGeneralShape].waves>;
+  static const int d = resident_per_cu(k_gtile<SH, double, double, false>, SH::NT);
+  static const int f = resident_per_cu(k_gtile<SH, float, float, false>, SH::NT);
+  return (f32 ? f : d) * device_cus();
+}
+
 hipError_t launch_general_grad(int f32, const void* gF, const void* X, int64_t n, int64_t M,
                                double* g, hipStream_t st) {
-  const unsigned grid = (unsigned)((n + kGridNT - 1) / kGridNT);
+  constexpr int64_t kFill = (int64_t)1 << 18;
+  if (!f32 && n >= kFill) {
+    hipLaunchKernelGGL(k_ggrad_rows<double>, dim3((unsigned)((n + kGridNT - 1) / kGridNT)),
+                       dim3(kGridNT), 0, st, static_cast<const double*>(gF),
+                       static_cast<const double*>(X), n, M, g);
+    return hipGetLastError();
+  }
+  // rows per workgroup: 1024 down to 16 (a cache line) until there are two
+  // workgroups per compute unit; slices until the device holds kFill threads
+  // (more only shorten the streams)
+  int rb = n >= kFill ? kGradNT : 256, sl = 1;
+  while (rb > 16 && n < (int64_t)rb * 2 * device_cus()) rb /= 2;
+  const unsigned grid = (unsigned)((n + rb - 1) / rb);
+  while (sl * rb < kGradNT && sl < M && (int64_t)grid * rb * sl < kFill) sl *= 2;
   if (f32)
-    hipLaunchKernelGGL(k_ggrad<float>, dim3(grid), dim3(kGridNT), 0, st,
-                       static_cast<const float*>(gF), static_cast<const float*>(X), n, M, g);
+    hipLaunchKernelGGL((k_ggrad<float, 2>), dim3(grid), dim3(rb * sl), 0, st,
+                       static_cast<const float*>(gF), static_cast<const float*>(X), n, M, rb, sl,
+                       g);
   else
-    hipLaunchKernelGGL(k_ggrad<double>, dim3(grid), dim3(kGridNT), 0, st,
-                       static_cast<const double*>(gF), static_cast<const double*>(X), n, M, g);
+    hipLaunchKernelGGL((k_ggrad<double, 1>), dim3(grid), dim3(rb * sl), 0, st,
+                       static_cast<const double*>(gF), static_cast<const double*>(X), n, M, rb,
+                       sl, g);
   return hipGetLastError();
 }
 
