@@ -1414,23 +1414,19 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     L.n_bins = L.n_sys = 0;
     L.n_beta = L.n_last = 0;
     L.nfull = 0;
-    // Right-hand sides per item: up to 8 share one load of a tile's constants
-    // (about the traffic of two right-hand sides), and the rounds of resident
-    // workgroups over the items should be full.  The fewest rounds times
-    // (R + 2): 24 right-hand sides of 123 tiles in double take R = 6 (one
-    // round, final pass 46 us; R = 2, 50 us), 300 of 10 tiles 6 (45 against
-    // 52 us), 64 of 256 tiles 8.
+    // Right-hand sides per item: up to 8 share one load of a tile's constants,
+    // as many as leave four items per compute unit; or as many as give just
+    // one round of resident workgroups, at least nine tenths of them busy (24
+    // right-hand sides of 123 tiles in double: R = 6, final pass 46 us, R = 2,
+    // 50 us; 300 of 10 tiles 45 against 52 us; but 30 of 39 tiles, three
+    // quarters busy, 27 against 25 us for the whole solve).
     const int64_t slots_g = std::max(1, tdt::general_slots(p->dtype == TDT_F32 ? 1 : 0));
-    int R = 1;
-    int64_t best = 0;
-    for (int r = 1; r <= 8 && r <= M; ++r) {
-      const int64_t items = nt * ((M + r - 1) / r);
-      const int64_t cost = (items + slots_g - 1) / slots_g * (r + 2);
-      if (best == 0 || cost <= best) {
-        best = cost;
-        R = r;
-      }
-    }
+    auto items_of = [&](int r) { return nt * ((M + r - 1) / r); };
+    const int rmax = (int)std::min<int64_t>(M, 8);
+    int R = rmax;
+    while (R > 1 && items_of(R) < 4 * (int64_t)tdt::device_cus()) --R;
+    for (int r = rmax; r >= 1; --r)   // (the fewest that do: even groups)
+      if (items_of(r) <= slots_g && 10 * items_of(r) >= 9 * slots_g) R = r;
     L.gen_R = R;
     const int64_t groups = (M + R - 1) / R;
     L.n_p1 = nt > 1 ? groups * nt : 0;
