@@ -443,8 +443,11 @@ tdt_status_t tdt_segment_merge(const double *l, const double *r, double *out);
  * interface pass across tiles, and the final pass (solve and store).  Where
  * every multi-tile system has at most 64 tiles the final pass runs the
  * interface pass itself, and the interface group is empty (two events with
- * nothing between them); a small series of whole tiles (at most 256 in all)
- * is solved by the final pass alone, and the first-pass group is empty too.
+ * nothing between them).  Where the Green rows of every multi-tile system
+ * have short supports (tdt_green_support; a ragged last tile at least as long
+ * as they need) the final pass forms the values outside its tiles from the
+ * rows next to their ends, and the first-pass group is empty too: the solve
+ * is one launch.  So are series of short systems, which share workgroups.
  * tdt_plan_profile_read synchronises the device, returns in ms3[0..2] the
  * summed milliseconds of the three groups over the recorded solves and in
  * *nsolves their number, and clears the record.  Disabling clears it too. */
@@ -460,7 +463,10 @@ tdt_status_t tdt_plan_profile_read(tdt_plan_t plan, double *ms3, int64_t *nsolve
  *       tile-parallel path (first pass, interface pass, final pass; the
  *       final pass runs the interface pass itself when every such system
  *       has at most 64 tiles).  0..16, default 8; 0 sends every multi-tile
- *       system through the tile-parallel path.
+ *       system through the tile-parallel path.  Without effect on batches
+ *       that are one launch anyway (short supports throughout, see
+ *       tdt_plan_profile), and on systems of at most 1024 rows where they are
+ *       all of the batch or many of it (a wavefront each).
  *   TDT_OPT_WG_PER_CU        0 (default): the tile kernels launch one
  *       workgroup per tile and the other kernels as many workgroups as fit
  *       at once; k > 0: every kernel runs at most k persistent workgroups

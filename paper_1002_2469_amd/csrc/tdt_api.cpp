@@ -106,6 +106,7 @@ struct tdt_plan_s {
     int* bins = nullptr;
     int* shorts = nullptr;  // systems of at most kShortItemNT blocks
     int64_t n_p1 = 0, n_ends = 0, n_fin = 0, n_grid = 0, n_whole = 0, n_bins = 0, n_short = 0;
+    bool halo = false;      // the final pass forms every tile's outside values
   } lists[2];
   int64_t vslots = 0, vfslots = 0;
   // workspace
@@ -678,6 +679,23 @@ void destroy(tdt_plan_s* p) {
   delete p;
 }
 
+// Whether the final pass should form its tiles' outside values itself, given
+// supports of `rows` rows (head and tail) and `tiles` tiles in all.  It saves
+// the first pass and the interface launch, about 10 us in all and, on large
+// solves, their time; it costs every tile the dot products of two wavefronts
+// the others wait for, which shows with long supports on many tiles, first in
+// float, whose tiles pass fastest.  Measured, launches apart and one launch
+// (us; double, refinement, float; supports head + tail):
+//   2^26 rows    64 + 64: 217/187  218/204  109/92   128 + 128: 209/183 220/203 109/93
+//               192 + 192: 216/202  227/208  114/127  384 + 384: 220/225 226/237 117/150
+//   300 x 30011 256 + 256: 42/36  51/42  27/26       576 + 576: 43/39  53/47  28/34
+//   65536 rows  576 + 576: 11.6/9.1  14.1/11.8  11.3/8.9
+bool halo_pays(tdt_dtype_t dtype, int64_t rows, int64_t tiles) {
+  if (dtype == TDT_F32)
+    return rows <= 256 || (rows <= 512 && tiles <= 2048) || tiles <= 256;
+  return rows <= 512 || tiles <= 2048;
+}
+
 // Work lists of a varlen plan.  Systems of at most kShortItemNT blocks take a
 // wavefront each (tdt_short.hip): a workgroup of the plan's shape would leave
 // three quarters of its lanes or more idle.  Systems of at most sys_max_tiles tiles are
@@ -689,10 +707,16 @@ tdt_status_t build_lists(tdt_plan_s* p, int dir, int max_tiles) {
   tdt_plan_s::Lists& q = p->lists[dir];
   std::vector<int2> p1, fin;
   std::vector<int> grid, whole_sys, shorts;
+  // (finish_plan sets halo for all of a batch's systems or none)
+  bool all_halo = false;
+  for (const SysDesc& D : p->hsys[dir]) all_halo = all_halo || D.halo;
+  std::vector<int2> halo;
   for (int64_t s : p->order) {
     const int nt = p->hsys[0][s].ntiles;
     if (p->short_ok[dir][s]) {
       shorts.push_back((int)s);
+    } else if (all_halo) {
+      for (int t = 0; t < nt; ++t) halo.push_back(make_int2((int)s, t));
     } else if (nt <= max_tiles) {
       whole_sys.push_back((int)s);
     } else {
@@ -708,6 +732,7 @@ tdt_status_t build_lists(tdt_plan_s* p, int dir, int max_tiles) {
     if (alone(it)) single.push_back(it);
   p1.erase(std::remove_if(p1.begin(), p1.end(), alone), p1.end());
   fin.assign(p1.rbegin(), p1.rend());
+  fin.insert(fin.end(), halo.begin(), halo.end());
   fin.insert(fin.end(), single.begin(), single.end());
   // full tiles of systems whose Green rows decay (in both directions), and
   // their last tiles where long enough: their summaries are dot products
@@ -774,6 +799,7 @@ tdt_status_t build_lists(tdt_plan_s* p, int dir, int max_tiles) {
   (void)hipFree(q.shorts);
   q = tdt_plan_s::Lists{};
   q.n_short = (int64_t)shorts.size();
+  q.halo = all_halo;
   q.n_p1 = (int64_t)p1.size();
   q.n_ends = (int64_t)ends.size();
   q.n_fin = (int64_t)fin.size();
@@ -941,9 +967,28 @@ tdt_status_t finish_plan(tdt_plan_s* p, const std::vector<double>& tm1,
         D.goff = (int64_t)pack.size();
         D.gkf = (int32_t)rf;
         D.gkl = (int32_t)rl;
+        D.halo = tl == kTile || D.glast;
         for (ld v : head) pack.push_back((double)v);
         for (ld v : tail) pack.push_back((double)v);
       }
+      // The outside values formed in the final pass, if that can be done for
+      // every system with an interface pass: then the batch is that launch
+      // alone (next to one of short systems), whatever the sizes.  With one
+      // system that needs the first pass (or the whole-system kernel) its
+      // launch is there anyway, and the others do better in it:
+      // separation-of-variables batch 94.5 us, 98 with them in the final pass
+      // alone; 1000 quasi-Toeplitz systems with refinement 149 and 182.
+      bool all = true;
+      int64_t rows = 0, tiles = 0;
+      for (int64_t s = 0; s < S; ++s) {
+        const SysDesc& D = p->hsys[dir][s];
+        if (p->short_ok[dir][s]) continue;
+        tiles += D.ntiles;
+        rows = std::max<int64_t>(rows, D.gkf + D.gkl);
+        if (needs_interface(D) && !D.halo) all = false;
+      }
+      if (!all || !halo_pays(p->dtype, rows, tiles))
+        for (SysDesc& D : p->hsys[dir]) D.halo = 0;
       (void)hipFree(p->dgpack[dir]);
       p->dgpack[dir] = nullptr;
       if (!pack.empty()) {
@@ -966,6 +1011,15 @@ tdt_status_t finish_plan(tdt_plan_s* p, const std::vector<double>& tm1,
       int64_t kf = 0, kl = 0;
       green_support(r1, r2, kf, kl);
       green_support_rounded(kTile, kf, kl, p->green_kf[dir], p->green_kl[dir]);
+      {
+        SysDesc& D = p->hsys[dir][0];
+        const int rf = p->green_kf[dir], rl = p->green_kl[dir];
+        const int64_t tl = D.n - (int64_t)(D.ntiles - 1) * kTile;
+        int64_t bf = 0, bl = 0, C = 0;
+        D.halo = rf > 0 &&
+                 (tl == kTile || (green_support_bound(a, t0[0], c, kTile, bf, bl, nullptr, &C) &&
+                                  tl >= std::max(rf, rl) + C));
+      }
       tdt_status_t sg = dev_upload(&p->dgreen[dir], g.data(), g.size());
       if (sg != TDT_OK) return sg;
     }
@@ -1454,6 +1508,7 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     L.ends_items = q.n_ends > 0 ? q.ends : nullptr;
     L.n_ends = q.n_ends;
     L.gpack = p->dgpack[dir];
+    L.halo = q.halo ? 1 : 0;
     L.short_items = q.shorts;
     L.n_short = q.n_short;
     slots = p->vslots;
@@ -1462,7 +1517,11 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
   } else {
     const SysDesc& D0 = p->hsys[0][0];
     const int64_t nt = D0.ntiles;
-    const bool itf = needs_interface(D0);
+    const bool need = needs_interface(D0);
+    const bool itf =
+        need && !(p->hsys[dir][0].halo &&
+                  halo_pays(p->dtype, p->green_kf[dir] + p->green_kl[dir], M * nt));
+    L.halo = need && !itf ? 1 : 0;
     L.p1_items = nullptr;
     L.fin_items = nullptr;
     L.grid_items = nullptr;
@@ -1481,7 +1540,7 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     L.n_fin = M * nt;
     short_runs(p, dir, M, L.short_nt, L.short_g, L.short_runs);
     L.short_M = M;
-    slots = itf ? M * D0.tslots : 0;
+    slots = need ? M * D0.tslots : 0;
     fslots = adjoint ? series_fslots(p, M) : 0;
     L.corner0 = M * nt;
   }

@@ -140,6 +140,15 @@ __device__ __forceinline__ double wave_max(double v) {
   return fmax(fmax(readlane(v, 15), readlane(v, 31)), fmax(readlane(v, 47), readlane(v, 63)));
 }
 
+// Sum over the 64 lanes in a fixed order (all lanes receive it).
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp<0x111>(0.0, v);
+  v += dpp<0x112>(0.0, v);
+  v += dpp<0x114>(0.0, v);
+  v += dpp<0x118>(0.0, v);
+  return (readlane(v, 15) + readlane(v, 31)) + (readlane(v, 47) + readlane(v, 63));
+}
+
 constexpr int kDppRowShr = 0x110;   // + d: row_shr:d
 constexpr int kDppRowShl = 0x100;   // + d: row_shl:d
 

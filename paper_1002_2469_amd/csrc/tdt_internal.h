@@ -75,6 +75,11 @@ struct SysDesc {
   // a workgroup's table loads touch a few cache lines (0: every lane reads
   // its own entry)
   int32_t tfix;
+  // 1: the final pass can form the values outside the system's tiles itself,
+  // from the supports next to each tile's ends (struct Halo): the system has
+  // supports, and its last tile is long enough for their entries
+  int32_t halo;
+  int32_t pad;
 };
 // First pass from the Green rows' supports: supports longer than this many
 // rows (head and tail together) take a wavefront per tile end, shorter ones
@@ -163,6 +168,7 @@ struct LaunchSet {
   const double* qtab64;   // quasi-Toeplitz: [ncidx][2 qnt + kQTabN]
   const float* qtab32;
   int qnt;
+  int halo;               // the final pass forms its tiles' outside values (SysDesc halo)
   int64_t corner0;        // series, quasi-Toeplitz: first corner t-gradient slot
   int quasi;              // the plan's systems are quasi-Toeplitz
   // general (per-row) matrix, series plans: per-row LU and per-block constants

@@ -204,7 +204,9 @@ __device__ __forceinline__ void lane_ghosts(const Seg<T>& pre, const Seg<T>& suf
 // and the lanes past the end pass both recurrences through unchanged
 // (A = C = 1, g = h = 0), so that the tile's last unknown is the one of its
 // real last row.
-template <class SH, typename Tc, bool FULL, bool TAILV = false>
+// EDGE: XLt is valid in the first wavefront and XRt in the last one only, and
+// they enter through those wavefronts' totals.
+template <class SH, typename Tc, bool FULL, bool TAILV = false, bool EDGE = false>
 __device__ __forceinline__ void tile_solve(Tc (&q)[SH::B], int len_in, Tc XLt, Tc XRt,
                                            const Consts<Tc>& K, Tc bp, Tc iDf,
                                            Tc (*fw)[2], Tc (*bw)[2], double* yfo,
@@ -263,9 +265,9 @@ __device__ __forceinline__ void tile_solve(Tc (&q)[SH::B], int len_in, Tc XLt, T
   Tc A = pl * iD;
   Tc g = yl + A * bp * yf;
   wave_scan_affine_fwd(A, g);
-  if (lane == 63) { fw[w][0] = A; fw[w][1] = g; }
+  if (lane == 63) { fw[w][0] = A; fw[w][1] = EDGE && w == 0 ? A * XLt + g : g; }
   __syncthreads();
-  Tc cin = XLt;
+  Tc cin = EDGE && w != 0 ? Tc(0) : XLt;
   for (int k = 0; k < w; ++k) cin = fw[k][0] * cin + fw[k][1];
   const Tc alpha = A * cin + g;
   Tc alpha_prev = __shfl_up(alpha, 1, 64);
@@ -274,9 +276,9 @@ __device__ __forceinline__ void tile_solve(Tc (&q)[SH::B], int len_in, Tc XLt, T
   Tc C = cf * iD;
   Tc h = (yf + pf * alpha_prev) * iD;
   wave_scan_affine_bwd(C, h);
-  if (lane == 0) { bw[w][0] = C; bw[w][1] = h; }
+  if (lane == 0) { bw[w][0] = C; bw[w][1] = EDGE && w == kNW - 1 ? C * XRt + h : h; }
   __syncthreads();
-  Tc ein = XRt;
+  Tc ein = EDGE && w != kNW - 1 ? Tc(0) : XRt;
   for (int k = kNW - 1; k > w; --k) ein = bw[k][0] * ein + bw[k][1];
   const Tc u = C * ein + h;
   if (TAILV || yfo) {
@@ -347,10 +349,8 @@ struct TileArgs {
   int64_t ttab_n;
   int64_t corner0;                    // series, quasi-Toeplitz: first corner slot (2 per
                                       // right-hand side) of the adjoint partials
-  // final pass of a small series whose Green rows have short supports (the
-  // P1 kernels): each workgroup also computes its system's tile summaries
-  // (no first-pass launch); the supports' entries as the first pass's
-  // ([2][tile length])
+  // final pass of a series with short supports (SysDesc halo): the supports'
+  // entries as the first pass's ([2][tile length]; varlen: gpack)
   const double* __restrict__ green;
   int gkf, gkl;
 };
@@ -473,11 +473,175 @@ __device__ __forceinline__ void inline_ghosts(const SysDesc& S, int t, double u,
   XR = __shfl(un, t, 64);
 }
 
+// One wavefront's dot product of k rows of a tile with k entries of a Green
+// row's support (k a multiple of 64; both pointers already offset by the
+// lane), U rows in flight per lane.  The lane sums are added by a fixed
+// butterfly, so the result is repeatable and the same in every lane.
+// Both ends of a tile in one wavefront: H rows of the head and H of the tail
+// in flight together per lane (for short supports, where a wavefront per end
+// would cost more to launch than it saves in waiting).
+template <typename Tio, int H>
+__device__ __forceinline__ void support_dot2(const Tio* head, const double* gf, int kf,
+                                             const Tio* tail, const double* gl, int kl,
+                                             double& s1, double& s2) {
+  const int nf = kf / 64, nl = kl / 64;
+  s1 = 0.0;
+  s2 = 0.0;
+  for (int j0 = 0; j0 < nf || j0 < nl; j0 += H) {
+    double v[H], w[H], x[H], y[H];
+#pragma unroll
+    for (int u = 0; u < H; ++u) {
+      v[u] = j0 + u < nf ? (double)head[(j0 + u) * 64] : 0.0;
+      w[u] = j0 + u < nf ? gf[(j0 + u) * 64] : 0.0;
+      x[u] = j0 + u < nl ? (double)tail[(j0 + u) * 64] : 0.0;
+      y[u] = j0 + u < nl ? gl[(j0 + u) * 64] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < H; ++u) {
+      s1 += v[u] * w[u];
+      s2 += x[u] * y[u];
+    }
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    s1 += __shfl_xor(s1, d, 64);
+    s2 += __shfl_xor(s2, d, 64);
+  }
+}
+
+template <typename Tio, int U>
+__device__ __forceinline__ double support_dot(const Tio* rows, const double* g, int k) {
+  const int nr = k / 64;
+  double s = 0.0;
+  for (int j0 = 0; j0 < nr; j0 += U) {
+    double v[U], w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u] = j0 + u < nr ? (double)rows[(j0 + u) * 64] : 0.0;
+      w[u] = j0 + u < nr ? g[(j0 + u) * 64] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += v[u] * w[u];
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
+  return s;
+}
+
+// The values just outside a tile of a system whose Green rows have short
+// supports (SysDesc halo).  A tile's end values then vanish across it (its
+// response at the far end to an outside value is below 2^-60), so of the
+// recurrences of eq. (15) only the neighbouring tiles' summaries are left:
+//   alpha_{t-1} = y_last(t-1),  u_t = (y_first(t) + Pf alpha_{t-1}) iD_t,
+//   x_left(t) = alpha_{t-1} + beta_{t-1} u_t,  x_right(t) = u_{t+1}.
+// The first wavefront forms the left value and the last one the right value,
+// each from two dot products over the supports next to its end of the tile
+// (as the first pass), so the solve is one launch: no first pass, no
+// interface pass, no workspace.  Outside the chain of tiles: zero, or a
+// quasi-Toeplitz system's corner rows, whose unknowns these values are.  XL
+// is valid in the first wavefront, XR in the last.
+//   Supports of up to 128 rows each (kPre runs of 64 per lane) are requested
+// before the tile's own rows (request), so that their latency is shared;
+// longer ones are read when their turn comes.
+template <class SH, typename Tio, bool QUASI>
+struct Halo {
+  static constexpr int kPre = 2;
+  Tio fh[kPre], ft[kPre];
+  double gh[kPre], gt[kPre];
+  double bp, iD, fc;
+  const Tio *hd, *tl;
+  const double *gf, *gl;
+  int nf, nl;   // runs of the head and tail dot products (0: not needed)
+  bool pre;
+
+  __device__ __forceinline__ void request(const TileArgs<Tio>& A, const SysDesc& S,
+                                          const TileGeom& G) {
+    TDT_SHAPE(SH)
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool varlen = A.items != nullptr;
+    const int t = G.I.t, P = S.ntiles;
+    const int kf = varlen ? S.gkf : A.gkf, kl = varlen ? S.gkl : A.gkl;
+    gf = (varlen ? A.gpack + S.goff : A.green) + lane;
+    gl = varlen ? gf + kf : gf + 2 * kTile - kl;
+    nf = nl = 0;
+    bp = iD = fc = 0.0;
+    pre = true;
+    const bool left = w == 0 && (t > 0 || QUASI), right = w == kNW - 1 && (t < P - 1 || QUASI);
+    if (!left && !right) return;
+    // the boundary between tiles u - 1 and u: head of u, tail of u - 1 (the
+    // chain's two ends have only one of them, and a corner row's right-hand side)
+    const int u = left ? t : t + 1;
+    hd = A.F + G.base + (left ? 0 : G.tl) + lane;
+    tl = hd - kl;
+    nf = u < P ? kf / 64 : 0;
+    nl = u > 0 ? kl / 64 : 0;
+    if (u < P) {
+      const int64_t pos = tile_slot(S, 0, u, varlen);
+      bp = as_const(A.ttab)[pos];
+      iD = as_const(A.ttab)[A.ttab_n + pos];
+    }
+    if (QUASI && u == 0) fc = (double)A.F[G.base - 1];
+    if (QUASI && u == P) fc = (double)A.F[G.base + G.tl];
+    pre = nf <= kPre && nl <= kPre;
+    if (pre) {
+#pragma unroll
+      for (int r = 0; r < kPre; ++r) {
+        fh[r] = r < nf ? hd[r * 64] : Tio(0);
+        gh[r] = r < nf ? gf[r * 64] : 0.0;
+        ft[r] = r < nl ? tl[r * 64] : Tio(0);
+        gt[r] = r < nl ? gl[r * 64] : 0.0;
+      }
+    }
+  }
+
+  __device__ __forceinline__ void finish(const SysDesc& S, int t, double& XL, double& XR) {
+    TDT_SHAPE(SH)
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int P = S.ntiles;
+    XL = XR = 0.0;
+    const bool left = w == 0 && (t > 0 || QUASI), right = w == kNW - 1 && (t < P - 1 || QUASI);
+    if (!left && !right) return;
+    double h = 0.0, y = 0.0;
+    if (pre) {
+#pragma unroll
+      for (int r = 0; r < kPre; ++r) {
+        h += (double)fh[r] * gh[r];
+        y += (double)ft[r] * gt[r];
+      }
+    } else {
+      for (int j0 = 0; j0 < nf || j0 < nl; j0 += 4) {
+        double a[4], b[4], c[4], d[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          a[r] = j0 + r < nf ? (double)hd[(j0 + r) * 64] : 0.0;
+          b[r] = j0 + r < nf ? gf[(j0 + r) * 64] : 0.0;
+          c[r] = j0 + r < nl ? (double)tl[(j0 + r) * 64] : 0.0;
+          d[r] = j0 + r < nl ? gl[(j0 + r) * 64] : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          h += a[r] * b[r];
+          y += c[r] * d[r];
+        }
+      }
+    }
+    h = wave_sum(h);
+    y = wave_sum(y);
+    const int u = left ? t : t + 1;
+    const double pf = u == P - 1 ? S.ltileK[0] : S.tileK[0];
+    if (QUASI && u == 0) y = fc * S.qc[0];   // alpha_{-1}
+    const double uu = QUASI && u == P ? (fc * S.qc[2] + S.qc[3] * y) * S.qc[5] : (h + pf * y) * iD;
+    if (left) XL = y + bp * uu;
+    else XR = uu;
+  }
+};
+
 //   INLINE: the kernel can run the interface pass inline (when A.itf_inline)
-//   P1: the system's tile summaries are in LDS (ps), computed by the workgroup
-template <class SH, typename Tio, typename Tc, bool SUMMARY, bool QUASI, bool INLINE, bool P1>
+//   HALO: the kernel of a plan that forms the outside values itself
+template <class SH, typename Tio, typename Tc, bool SUMMARY, bool QUASI, bool INLINE, bool HALO>
 __device__ __forceinline__ void load_tile_item(const TileArgs<Tio>& A, int64_t item,
-                                               TileLoad<SH, Tio, Tc>& P, const double* ps) {
+                                               TileLoad<SH, Tio, Tc>& P) {
   TDT_SHAPE(SH)
   const int tid = threadIdx.x;
   const TileGeom G = tile_geom<SH>(A.items, A.sys, item, A.last_only);
@@ -486,6 +650,8 @@ __device__ __forceinline__ void load_tile_item(const TileArgs<Tio>& A, int64_t i
   // while the tile's rows are still on their way
   const bool inl = INLINE && !SUMMARY && A.itf_inline && (S.ntiles > 1 || QUASI);
   const int64_t sbase = G.base - G.t0;   // the system's first row (inside the corners)
+  [[maybe_unused]] Halo<SH, Tio, QUASI> H;
+  if constexpr (HALO) H.request(A, S, G);
   double iu = 0.0, iv = 0.0, ib = 0.0, ii = 1.0, fl = 0.0, fr = 0.0;
   if (inl) {
     const int lane = tid & 63;
@@ -493,8 +659,8 @@ __device__ __forceinline__ void load_tile_item(const TileArgs<Tio>& A, int64_t i
     const bool varlen = A.items != nullptr;
     const int64_t sl = tile_slot(S, G.I.m, tc, varlen);
     const int64_t tb = varlen ? sl : tile_slot(S, 0, tc, false);
-    iu = P1 ? ps[2 * tc] : A.summ[2 * sl];
-    iv = P1 ? ps[2 * tc + 1] : A.summ[2 * sl + 1];
+    iu = A.summ[2 * sl];
+    iv = A.summ[2 * sl + 1];
     ib = A.ttab[tb];
     ii = A.ttab[A.ttab_n + tb];
     if (QUASI) {
@@ -516,14 +682,17 @@ __device__ __forceinline__ void load_tile_item(const TileArgs<Tio>& A, int64_t i
     P.bp = tb[kTabBeta * kNT + ti];
     P.iD = tb[kTabInvD * kNT + ti];
   }
-  if (inl) {
+  if constexpr (HALO)
+    H.finish(S, G.I.t, P.XL, P.XR);
+  else if (inl)
     inline_ghosts<QUASI>(S, G.I.t, iu, iv, ib, ii, fl, fr, P.XL, P.XR);
-    if (QUASI && tid == 0 && (G.I.t == 0 || G.I.t == S.ntiles - 1)) {
+  if (HALO || inl) {
+    if (QUASI) {
       // the corner rows (and, in the adjoint, their t-gradient partials)
       const int64_t cs0 = A.items ? (int64_t)S.fslot0 + S.ntiles : A.corner0 + 2 * G.I.m;
-      if (G.I.t == 0)
+      if (tid == 0 && G.I.t == 0)
         store_corner<Tio>(A.X, A.Xfwd, A.gpart + kGradN * cs0, sbase, S.n, 0, P.XL);
-      if (G.I.t == S.ntiles - 1)
+      if (tid == kNT - 64 && G.I.t == S.ntiles - 1)
         store_corner<Tio>(A.X, A.Xfwd, A.gpart + kGradN * (cs0 + 1), sbase, S.n, 1, P.XR);
     }
   } else if (!SUMMARY) {
@@ -554,55 +723,8 @@ struct TileShared {
   Tc fw[SH::NW][2], bw[SH::NW][2];
   double red[SH::NW][4];
   double edge[SH::NW][2];
-  double ps[64][2];   // a small series system's tile summaries (final pass)
+  double xr;          // a folded right outside value (quasi-Toeplitz)
 };
-
-// The tile summaries of one system of a small series from the Green rows'
-// supports (the dot products of the first pass, eq. (13)), computed by the
-// final pass's workgroup itself: wavefront w takes tiles w, w + NW, ...,
-// four at a time with all their loads in flight; lanes stride the support
-// rows and the lane sums are added by the same butterfly as in the first
-// pass.  Results to ps (LDS); the caller's barrier publishes them.
-template <class SH, typename Tio>
-__device__ __forceinline__ void system_summaries(const TileArgs<Tio>& A, const SysDesc& S,
-                                                 int64_t sbase, double (*ps)[2]) {
-  TDT_SHAPE(SH)
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int nf = A.gkf / 64, nl = A.gkl / 64;
-  const double* gf = A.green + lane;
-  const double* gl = A.green + 2 * kTile - A.gkl + lane;
-  for (int t0 = w; t0 < S.ntiles; t0 += 4 * kNW) {
-    double s1[4], s2[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) s1[q] = s2[q] = 0.0;
-    for (int j = 0; j < nf || j < nl; ++j) {
-      const double g1 = j < nf ? gf[j * 64] : 0.0, g2 = j < nl ? gl[j * 64] : 0.0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int t = t0 + q * kNW;
-        const Tio* head = A.F + sbase + (int64_t)(t < S.ntiles ? t : 0) * kTile + lane;
-        const double h = j < nf ? (double)head[j * 64] : 0.0;
-        const double l = j < nl ? (double)head[kTile - A.gkl + j * 64] : 0.0;
-        s1[q] += h * g1;
-        s2[q] += l * g2;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) {
-        s1[q] += __shfl_xor(s1[q], d, 64);
-        s2[q] += __shfl_xor(s2[q], d, 64);
-      }
-      const int t = t0 + q * kNW;
-      if (lane == 0 && t < S.ntiles) {
-        ps[t][0] = s1[q];
-        ps[t][1] = s2[q];
-      }
-    }
-  }
-}
 
 // Element j*kNT + tid of a tile lives in LDS row j*(kNT/kB) + tid/kB, column
 // tid%kB: after the coalesced loads each lane owns kB consecutive rows.
@@ -631,7 +753,7 @@ __device__ __forceinline__ int block_len(int tl) {
 // block has kB rows.  REFINE: Tio = double data, Tc = float sweeps; residual
 // and update in double, repeated until converged (see below).
 template <class SH, typename Tio, typename Tc, bool REFINE, bool SUMMARY, bool FULL,
-          bool TAILV = false>
+          bool TAILV = false, bool EDGE = false>
 __device__ __forceinline__ void solve_in_lds(TileShared<SH, Tio, Tc>& sh, Tio* myrow, int len, int tl,
                                              double XLt, double XRt, const SysDesc& S,
                                              const Consts<Tc>& K, Tc bp, Tc iDf,
@@ -646,7 +768,7 @@ __device__ __forceinline__ void solve_in_lds(TileShared<SH, Tio, Tc>& sh, Tio* m
     if constexpr (SUMMARY) {
       tile_solve<SH, Tc, FULL, TAILV>(q, len, Tc(0), Tc(0), K, bp, iDf, sh.fw, sh.bw, yfo, ylo);
     } else {
-      tile_solve<SH, Tc, FULL>(q, len, (Tc)XLt, (Tc)XRt, K, bp, iDf, sh.fw, sh.bw, (double*)nullptr,
+      tile_solve<SH, Tc, FULL, false, EDGE>(q, len, (Tc)XLt, (Tc)XRt, K, bp, iDf, sh.fw, sh.bw, (double*)nullptr,
                            (double*)nullptr);
 #pragma unroll
       for (int i = 0; i < kB; ++i) myrow[i] = (Tio)q[i];
@@ -755,7 +877,8 @@ __device__ __forceinline__ void solve_in_lds(TileShared<SH, Tio, Tc>& sh, Tio* m
   }
 }
 
-template <class SH, typename Tio, typename Tc, bool REFINE, bool SUMMARY, bool TAILV = false>
+template <class SH, typename Tio, typename Tc, bool REFINE, bool SUMMARY, bool TAILV = false,
+          bool EDGE = false>
 __device__ __forceinline__ void solve_tile_lds(TileShared<SH, Tio, Tc>& sh, int tl, double XLt,
                                                double XRt, const SysDesc& S,
                                                const Consts<Tc>& K, Tc bp, Tc iDf, double* yfo,
@@ -766,10 +889,10 @@ __device__ __forceinline__ void solve_tile_lds(TileShared<SH, Tio, Tc>& sh, int 
   // a separate full-tile copy of the solve (no tail masking) pays in the
   // refinement kernel; in the double ones it measured the same time
   if (REFINE && tl == kTile)
-    solve_in_lds<SH, Tio, Tc, REFINE, SUMMARY, true, TAILV>(sh, myrow, kB, tl, XLt, XRt, S, K, bp, iDf, yfo, ylo,
+    solve_in_lds<SH, Tio, Tc, REFINE, SUMMARY, true, TAILV, EDGE>(sh, myrow, kB, tl, XLt, XRt, S, K, bp, iDf, yfo, ylo,
                                         it_max, est_max, max_iter, refine_tol);
   else
-    solve_in_lds<SH, Tio, Tc, REFINE, SUMMARY, false, TAILV>(sh, myrow, block_len<SH>(tl), tl, XLt, XRt, S, K, bp, iDf,
+    solve_in_lds<SH, Tio, Tc, REFINE, SUMMARY, false, TAILV, EDGE>(sh, myrow, block_len<SH>(tl), tl, XLt, XRt, S, K, bp, iDf,
                                          yfo, ylo, it_max, est_max, max_iter, refine_tol);
 }
 
@@ -895,61 +1018,6 @@ __device__ __forceinline__ void fold_right(TileShared<SH, Tio, Tc>& sh, int tl, 
   }
 }
 
-// One wavefront's dot product of k rows of a tile with k entries of a Green
-// row's support (k a multiple of 64; both pointers already offset by the
-// lane), U rows in flight per lane.  The lane sums are added by a fixed
-// butterfly, so the result is repeatable and the same in every lane.
-// Both ends of a tile in one wavefront: H rows of the head and H of the tail
-// in flight together per lane (for short supports, where a wavefront per end
-// would cost more to launch than it saves in waiting).
-template <typename Tio, int H>
-__device__ __forceinline__ void support_dot2(const Tio* head, const double* gf, int kf,
-                                             const Tio* tail, const double* gl, int kl,
-                                             double& s1, double& s2) {
-  const int nf = kf / 64, nl = kl / 64;
-  s1 = 0.0;
-  s2 = 0.0;
-  for (int j0 = 0; j0 < nf || j0 < nl; j0 += H) {
-    double v[H], w[H], x[H], y[H];
-#pragma unroll
-    for (int u = 0; u < H; ++u) {
-      v[u] = j0 + u < nf ? (double)head[(j0 + u) * 64] : 0.0;
-      w[u] = j0 + u < nf ? gf[(j0 + u) * 64] : 0.0;
-      x[u] = j0 + u < nl ? (double)tail[(j0 + u) * 64] : 0.0;
-      y[u] = j0 + u < nl ? gl[(j0 + u) * 64] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < H; ++u) {
-      s1 += v[u] * w[u];
-      s2 += x[u] * y[u];
-    }
-  }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    s1 += __shfl_xor(s1, d, 64);
-    s2 += __shfl_xor(s2, d, 64);
-  }
-}
-
-template <typename Tio, int U>
-__device__ __forceinline__ double support_dot(const Tio* rows, const double* g, int k) {
-  const int nr = k / 64;
-  double s = 0.0;
-  for (int j0 = 0; j0 < nr; j0 += U) {
-    double v[U], w[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      v[u] = j0 + u < nr ? (double)rows[(j0 + u) * 64] : 0.0;
-      w[u] = j0 + u < nr ? g[(j0 + u) * 64] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) s += v[u] * w[u];
-  }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
-  return s;
-}
-
 // The same first pass when the two Green rows decay fast (a diagonally
 // dominant T, Sec. 3.4: the entries fall geometrically away from the row's
 // own end): the plan has found the head of the first row (kf entries) and
@@ -1071,10 +1139,10 @@ __device__ __forceinline__ void beta_ends_item(const BetaEndsArgs<Tio>& A, int64
 //                    in double, repeated until converged.
 //   BWD            : also accumulates the t-gradient partial sums against the
 //                    forward solution Xfwd (the tile solves T^T gF = gX).
-//   P1             : final pass of a small series that computes its
-//                    system's tile summaries itself (no first pass)
+//   HALO           : final pass that forms the values just outside its tiles
+//                    itself (no first pass, no interface pass)
 template <class SH, typename Tio, typename Tc, bool REFINE, bool SUMMARY, bool BWD, bool QUASI,
-          bool P1 = false>
+          bool HALO = false>
 __global__ __launch_bounds__(SH::NT, REFINE ? kRefineWaves : SH::WAVES) void k_tile(
     TileArgs<Tio> A) {
   TDT_SHAPE(SH)
@@ -1105,14 +1173,8 @@ __global__ __launch_bounds__(SH::NT, REFINE ? kRefineWaves : SH::WAVES) void k_t
   TileLoad<SH, Tio, Tc> P;
 
   while (k < A.nitems) {
-    if constexpr (P1) {
-      const TileGeom G0 = tile_geom<SH>(A.items, A.sys, item_of(k), A.last_only);
-      const SysDesc S0 = load_sys(A.sys, G0.I.s);
-      system_summaries<SH, Tio>(A, S0, G0.base - G0.t0, sh.ps);
-      __syncthreads();
-    }
-    load_tile_item<SH, Tio, Tc, SUMMARY, QUASI, !(REFINE && QUASI), P1>(A, item_of(k), P,
-                                                                        &sh.ps[0][0]);
+    load_tile_item<SH, Tio, Tc, SUMMARY, QUASI, !(REFINE && QUASI) && !HALO, HALO>(
+        A, item_of(k), P);
     const int64_t item = item_of(k);
     const TileGeom G = tile_geom<SH>(A.items, A.sys, item, A.last_only);
     const SysDesc S = load_sys(A.sys, G.I.s);
@@ -1129,10 +1191,11 @@ __global__ __launch_bounds__(SH::NT, REFINE ? kRefineWaves : SH::WAVES) void k_t
       for (int j = 0; j < kB; ++j) lw[j * lstride] = P.v[j];
     }
     const int64_t kn = k + gridDim.x;
-    __syncthreads();
     const bool fold = QUASI && !SUMMARY && tl < kTile;
+    if (fold && tid == kNT - 64) sh.xr = XRt;
+    __syncthreads();
     if (fold) {
-      fold_right<SH>(sh, tl, S.c, XRt);
+      fold_right<SH>(sh, tl, S.c, sh.xr);
       __syncthreads();
     }
 
@@ -1140,7 +1203,7 @@ __global__ __launch_bounds__(SH::NT, REFINE ? kRefineWaves : SH::WAVES) void k_t
       solve_tile_lds<SH, Tio, Tc, REFINE, true, QUASI>(sh, tl, 0.0, 0.0, S, K, bp, iDf, A.summ + 2 * slot,
                                       A.summ + 2 * slot + 1, it_max, est_max, A.max_iter, A.refine_tol);
     } else {
-      solve_tile_lds<SH, Tio, Tc, REFINE, false>(sh, tl, XLt, fold ? 0.0 : XRt, S, K, bp, iDf,
+      solve_tile_lds<SH, Tio, Tc, REFINE, false, false, HALO>(sh, tl, XLt, fold ? 0.0 : XRt, S, K, bp, iDf,
                                                  (double*)nullptr, (double*)nullptr, it_max,
                                                  est_max, A.max_iter, A.refine_tol);
       __syncthreads();
@@ -2017,8 +2080,8 @@ __global__ __launch_bounds__(NTG) void k_grid_affine_lean(GridArgs A) {
 // most), so that every thread keeps eight of them in flight.  Varlen plans:
 // one thread per system and component adds the system's slots in order, in
 // workgroups of one wavefront over the whole device (one thread per system
-// in workgroups of 512 took GTV0 us on 1000 quasi-Toeplitz systems, now GTV1
-// us).  Series plans: one workgroup adds all slots, thread k the slots k,
+// in workgroups of 512 took 10.7 us on 1000 quasi-Toeplitz systems, now
+// 5.2).  Series plans: one workgroup adds all slots, thread k the slots k,
 // k + 512, ..., then a fixed tree.
 constexpr int kGtItemNT = 64;
 __device__ __forceinline__ double sum_slots(const double* p, int64_t stride, int64_t n) {
@@ -2393,10 +2456,10 @@ static int64_t grid_cap(int per_cu, int wg_per_cu) {
 // against 5.3 TB/s for the same tile code run by resident workgroups that
 // loop over tiles).  With a cap per CU the workgroups persist and loop.
 template <class SH, typename Tio, typename Tc, bool REFINE, bool SUMMARY, bool BWD, bool QUASI,
-          bool P1 = false>
+          bool HALO = false>
 static void launch_tile(TileArgs<Tio>& A, int64_t nitems, int reverse, int last_only,
                         int wg_per_cu, hipStream_t st, int64_t extra_wg = 0) {
-  auto kern = k_tile<SH, Tio, Tc, REFINE, SUMMARY, BWD, QUASI, P1>;
+  auto kern = k_tile<SH, Tio, Tc, REFINE, SUMMARY, BWD, QUASI, HALO>;
   static int per_cu = resident_per_cu(kern, SH::NT);
   const int64_t cap = wg_per_cu > 0 ? grid_cap(per_cu, wg_per_cu) : nitems;
   A.nitems = nitems;
@@ -2685,15 +2748,9 @@ static hipError_t run_solve(const LaunchSet& L, const void* F, void* X, const vo
   // refinement of quasi-Toeplitz systems, whose final pass lost more to it
   // than the launch costs)
   const bool inl = L.n_grid > 0 && L.max_ntiles <= 64 && !(REFINE && QUASI);
-  // a small series (few tiles in all, at most four per wavefront of a
-  // workgroup) of whole tiles with short supports: the final pass computes
-  // the summaries too, and the solve is one launch
-  const bool p1i = inl && !QUASI && !BWD && L.green && L.green_kf > 0 && L.n_last == 0 &&
-                   L.n_beta > 0 && L.n_beta <= 256 && L.max_ntiles <= 4 * SH::NW &&
-                   L.green_kf + L.green_kl <= kEndsSplitRows;
   if (L.n_grid > 0) {
     if (L.green) {
-      if (L.n_beta > 0 && !p1i) {
+      if (L.n_beta > 0) {
         if (L.green_kf > 0)
           launch_beta_ends<SH, Tio>(L, static_cast<const Tio*>(F), st);
         else
@@ -2737,6 +2794,7 @@ static hipError_t run_solve(const LaunchSet& L, const void* F, void* X, const vo
   if (L.n_sys > 0) launch_sys<SH, Tio, Tc, REFINE, BWD, QUASI>(L, A, st);
   A.items = L.fin_items;
   A.itf_inline = inl ? 1 : 0;
+  A.gpack = L.gpack;
   A.green = L.green;
   A.gkf = L.green_kf;
   A.gkl = L.green_kl;
@@ -2744,16 +2802,11 @@ static hipError_t run_solve(const LaunchSet& L, const void* F, void* X, const vo
   // last while they are still cached: a series runs last-tile-first, a varlen
   // plan's list already starts with the first pass's tiles in reverse
   if (L.n_fin > 0) {
-    if constexpr (!BWD && !QUASI) {
-      if (p1i) {
-        launch_tile<SH, Tio, Tc, REFINE, false, false, false, true>(A, L.n_fin, 0, 0,
-                                                                   L.wg_per_cu, st);
-        if (L.ev) (void)hipEventRecord(L.ev[3], st);
-        return hipGetLastError();
-      }
-    }
-    launch_tile<SH, Tio, Tc, REFINE, false, BWD, QUASI>(
-        A, L.n_fin, (L.n_p1 > 0 && !L.fin_items) ? 1 : 0, 0, L.wg_per_cu, st);
+    const int rev = (L.n_p1 > 0 && !L.fin_items) ? 1 : 0;
+    if (L.halo)
+      launch_tile<SH, Tio, Tc, REFINE, false, BWD, QUASI, true>(A, L.n_fin, 0, 0, L.wg_per_cu, st);
+    else
+      launch_tile<SH, Tio, Tc, REFINE, false, BWD, QUASI>(A, L.n_fin, rev, 0, L.wg_per_cu, st);
   }
   if (L.ev) (void)hipEventRecord(L.ev[3], st);
   return hipGetLastError();
