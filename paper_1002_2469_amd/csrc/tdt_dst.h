@@ -15,6 +15,7 @@ constexpr int kDstPasses = 10;
 struct DstPlan {
   int n, np;
   int radix[kDstPasses];
+  int ns[kDstPasses], nb[kDstPasses], step[kDstPasses];   // Ns, n / R, n / (R Ns)
   uint32_t magic[kDstPasses];   // floor(2^31 / Ns) + 1, Ns the product of the radices before
   const double* sn;             // sin(pi j / n), j < n (device)
   const double* tw;             // e^{-2 pi i q / n}, q < n, complex (device)
@@ -29,24 +30,24 @@ hipError_t launch_dst_any_rows(const DstPlan& p, const double* in, double* out, 
                                int64_t ldi, int64_t ldo, double scale, hipStream_t st);
 // Columns: column c < M of batch b has entry i at b ldb + i ld + c; ld and ldb
 // even, 16-byte aligned arrays, columns in pairs (M odd: the entry after the
-// last column of every row exists).  out may be in.  Without g: out = S.
-// With g: the transform, times the factor of the ADI iterate, transformed
+// last column of every row exists).  out may be in.  Without ry: out =
+// S.  With ry: the transform, times the factor of the ADI iterate, transformed
 // again (the inverse up to the factor's scale):
-//   norm (1 - ry[b][c] rz[m][c]) / (ly[b] + lz[m] + mu[c]).
+//   norm (1 - ry[c][b] rz[c][m]) / (ly[b] + lz[m] + mu[c]).
 struct DstColumns {
   const double* in;
   double* out;
   int64_t M, ld, nb, ldb;
-  const double *ry, *rz;        // [nb][ldr], [n - 1][ldr], or null
+  const double *ry, *rz;        // [M][ldy], [M][ldz], or null
   const double *ly, *lz, *mu;
-  int64_t ldr;
+  int64_t ldy, ldz;
   double norm;
 };
 hipError_t launch_dst_columns(const DstPlan& p, const DstColumns& a, hipStream_t st);
-// out[l][c] = prod_{j < count[c]} (w[c][j] - x) / (w[c][j] + x), x = lam[l] +
+// out[c][l] = prod_{j < count[c]} (w[c][j] - x) / (w[c][j] + x), x = lam[l] +
 // mu[c] / 2: an ADI cycle's error factor in one direction (w: [M][jmax]).
 hipError_t launch_adi_factors(const double* w, const int* count, int jmax, const double* lam,
-                              const double* mu, int64_t L, int64_t M, int64_t ldr, double* out,
+                              const double* mu, int64_t L, int64_t M, double* out,
                               hipStream_t st);
 
 }  // namespace tdt

@@ -14,8 +14,8 @@
 // the 2D solve of 999 x 1499 points 89 -> 45 us, of 4094 x 4000 1437 -> 276 us (with the
 // in-place line solves it allows).
 //
-// Bound by HBM on large arrays (columns of 511 entries: 465 us for 2.15 GB,
-// 4.6 TB/s), by the passes' barriers on small ones.  68 to 127 VGPRs: the
+// Bound by HBM on large arrays (columns of 511 entries: 445 us for 2.15 GB,
+// 4.8 TB/s), by the passes' barriers on small ones.  68 to 124 VGPRs: the
 // addresses of one pass are hidden from the next (opaque), without which the
 // compiler kept them all (250 VGPRs, spills).
 #include <hip/hip_runtime.h>
@@ -73,6 +73,20 @@ template <> struct Trig<13> {
 __device__ __forceinline__ int opaque(int v) {
   asm volatile("" : "+v"(v));
   return v;
+}
+
+// Orders the LDS accesses of a sequence's T threads: a barrier where they span
+// wavefronts; inside one wavefront its LDS operations complete in order, and
+// only the compiler has to keep them so.
+template <int T>
+__device__ __forceinline__ void seq_sync() {
+  if constexpr (T > 64) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
 }
 
 // R-point DFT in place, X_k = sum_r v_r e^{-2 pi i r k / R}
@@ -140,15 +154,27 @@ __device__ __forceinline__ void dft(double2 (&v)[R]) {
   }
 }
 
+// A sequence in LDS: one entry of padding after every 8 (strides 1, 8 and 64
+// without bank conflicts).  at(base, off), off a multiple of 8 known to the
+// compiler: a constant distance from at(base), no address of its own.
+struct Seq {
+  double2* p;
+  __device__ __forceinline__ double2& operator()(int i) const { return p[i + (i >> 3)]; }
+  __device__ __forceinline__ double2& at(int base, int off) const {
+    return p[base + (base >> 3) + off / 8 * 9];
+  }
+};
+
 // One Stockham pass of radix R: butterfly b = q Ns + k takes the entries
 // b + r n/R, times W^{k r}, W = e^{-2 pi i / (Ns R)}, and writes q Ns R + k + r Ns.
-// T threads, n <= 8 T: a thread has at most ceil(8 / R) butterflies.  at(i):
-// entry i in LDS.
-template <int R, int T, class At>
-__device__ __forceinline__ void fft_pass(const At& at, int j, int n, int Ns, uint32_t magic,
-                                         const double2* __restrict__ tw) {
+// T threads, n <= 8 T: a thread has at most ceil(8 / R) butterflies.  N = 8 T:
+// n = N and Ns = NS, powers of two, so that every distance is a constant;
+// N = 0: pass `p` of the plan, Ns the product of the radices before.
+template <int R, int T, int N, int NS>
+__device__ __forceinline__ void fft_pass(const Seq& at, int j, const DstPlan& P, int p) {
   constexpr int MB = (8 + R - 1) / R;
-  const int nb = n / R, step = nb / Ns;
+  const auto* tw = reinterpret_cast<const double2*>(P.tw);
+  const int nb = N ? N / R : P.nb[p], Ns = N ? NS : P.ns[p], step = N ? N / R / NS : P.step[p];
   j = opaque(j);
   __builtin_assume(j >= 0 && j < T);
   double2 v[MB][R];
@@ -156,13 +182,13 @@ __device__ __forceinline__ void fft_pass(const At& at, int j, int n, int Ns, uin
 #pragma unroll
   for (int m = 0; m < MB; ++m) {
     const int b = j + T * m;
-    const int q = (int)__umulhi(2u * (uint32_t)b, magic), k = b - q * Ns;
-    base[m] = b < nb ? q * Ns * R + k : -1;
-    if (b < nb) {
+    const int q = N ? b / NS : (int)__umulhi(2u * (uint32_t)b, P.magic[p]), k = b - q * Ns;
+    base[m] = N || b < nb ? q * Ns * R + k : -1;
+    if (N || b < nb) {
       double2 w = make_double2(1.0, 0.0);
       if (Ns > 1) w = tw[k * step];
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[m][r] = at(b + r * nb);
+      for (int r = 0; r < R; ++r) v[m][r] = N ? at.at(b, r * nb) : at(b + r * nb);
       if (Ns > 1) {
         // W^{k r}: one table entry, its even powers by squares
         const double2 w2 = cmul(w, w);
@@ -178,44 +204,53 @@ __device__ __forceinline__ void fft_pass(const At& at, int j, int n, int Ns, uin
       dft<R>(v[m]);
     }
   }
-  __syncthreads();   // every thread has read the pass's inputs
+  seq_sync<T>();   // every thread has read the pass's inputs
 #pragma unroll
   for (int m = 0; m < MB; ++m)
-    if (base[m] >= 0) {
+    if (N || base[m] >= 0) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) at(base[m] + r * Ns) = v[m][r];
+      for (int r = 0; r < R; ++r) {
+        if constexpr (N == 0) at(base[m] + r * Ns) = v[m][r];
+        else if constexpr (NS == 1) at.p[base[m] / 8 * 9 + r] = v[m][r];   // (R = 8)
+        else at.at(base[m], r * NS) = v[m][r];
+      }
     }
-  __syncthreads();
+  seq_sync<T>();
 }
 
-template <int T, class At>
-__device__ __forceinline__ void fft(const At& at, int j, const DstPlan& P) {
-  const auto* tw = reinterpret_cast<const double2*>(P.tw);
-  int Ns = 1;
-  for (int p = 0; p < P.np; ++p) {
-    const int R = P.radix[p];
-    const uint32_t mg = P.magic[p];
-    if (R == 8) fft_pass<8, T>(at, j, P.n, Ns, mg, tw);
-    else if (R == 4) fft_pass<4, T>(at, j, P.n, Ns, mg, tw);
-    else if (R == 2) fft_pass<2, T>(at, j, P.n, Ns, mg, tw);
-    else if (R == 3) fft_pass<3, T>(at, j, P.n, Ns, mg, tw);
-    else if (R == 5) fft_pass<5, T>(at, j, P.n, Ns, mg, tw);
-    else if (R == 7) fft_pass<7, T>(at, j, P.n, Ns, mg, tw);
-    else if (R == 11) fft_pass<11, T>(at, j, P.n, Ns, mg, tw);
-    else fft_pass<13, T>(at, j, P.n, Ns, mg, tw);
-    Ns *= R;
+template <int T, int N, int NS = 1>
+__device__ __forceinline__ void fft(const Seq& at, int j, const DstPlan& P) {
+  if constexpr (N > 0) {
+    static_assert(N == 8 * T && N >= 64, "the first radix is 8");
+    if constexpr (NS < N) {
+      constexpr int R = N / NS >= 8 ? 8 : N / NS;
+      fft_pass<R, T, N, NS>(at, j, P, 0);
+      fft<T, N, NS * R>(at, j, P);
+    }
+  } else {
+    for (int p = 0; p < P.np; ++p) {
+      const int R = P.radix[p];
+      if (R == 8) fft_pass<8, T, 0, 0>(at, j, P, p);
+      else if (R == 4) fft_pass<4, T, 0, 0>(at, j, P, p);
+      else if (R == 2) fft_pass<2, T, 0, 0>(at, j, P, p);
+      else if (R == 3) fft_pass<3, T, 0, 0>(at, j, P, p);
+      else if (R == 5) fft_pass<5, T, 0, 0>(at, j, P, p);
+      else if (R == 7) fft_pass<7, T, 0, 0>(at, j, P, p);
+      else if (R == 11) fft_pass<11, T, 0, 0>(at, j, P, p);
+      else fft_pass<13, T, 0, 0>(at, j, P, p);
+    }
   }
 }
 
 // The transforms of the pair from its spectrum: entry m (1 <= m < n) becomes
-// (S^A_m, S^B_m).  LS lanes lie between a sequence's neighbouring threads
-// (rows: 1, columns: the pairs side by side), wt: the wavefronts' totals of
-// each pair.  Ends with a barrier.
-template <int T, int LS, class At>
-__device__ __forceinline__ void split_scan(const At& at, int j, int n, double2* wt) {
-  constexpr int EP = 5;                          // ceil((n / 2 + 1) / T) <= 5
-  constexpr int JW = T * LS < 64 ? T : 64 / LS;  // threads of a sequence per wavefront
-  const int K1 = n / 2 + 1, ep = (K1 + T - 1) / T;
+// (S^A_m, S^B_m).  wt: the wavefronts' totals of the pair.  Ends synchronised.
+template <int T, int N>
+__device__ __forceinline__ void split_scan(const Seq& at, int j, int n, double2* wt) {
+  constexpr int EP = 4;                          // ceil(K1 / T) <= 4
+  constexpr int JW = T < 64 ? T : 64;            // threads of a sequence per wavefront
+  // (entry n / 2 of an even n belongs to no coefficient below n)
+  const int K1 = N ? N / 2 : (n + 1) / 2, ep = N ? EP : (K1 + T - 1) / T;
+  if (N) n = N;
   j = opaque(j);
   __builtin_assume(j >= 0 && j < T);
   double2 v[EP], im[EP];
@@ -223,7 +258,7 @@ __device__ __forceinline__ void split_scan(const At& at, int j, int n, double2* 
   for (int e = 0; e < EP; ++e) {
     const int k = j * ep + e;
     v[e] = im[e] = make_double2(0.0, 0.0);
-    if (e < ep && k < K1) {
+    if (N || (e < ep && k < K1)) {
       const double2 a = at(k), b = at(k == 0 ? 0 : n - k);
       const double h = k == 0 ? 0.25 : 0.5;   // Re Y_0 counts half
       v[e] = make_double2(h * (a.x + b.x), h * (a.y + b.y));
@@ -236,7 +271,7 @@ __device__ __forceinline__ void split_scan(const At& at, int j, int n, double2* 
   const int jl = j % JW;
 #pragma unroll
   for (int d = 1; d < JW; d <<= 1) {
-    const double yx = __shfl_up(x.x, d * LS, 64), yy = __shfl_up(x.y, d * LS, 64);
+    const double yx = __shfl_up(x.x, d, 64), yy = __shfl_up(x.y, d, 64);
     if (jl >= d) {
       x.x += yx;
       x.y += yy;
@@ -250,17 +285,17 @@ __device__ __forceinline__ void split_scan(const At& at, int j, int n, double2* 
     for (int q = 0; q < j / JW; ++q) c = cadd(c, wt[q]);
     off = cadd(off, c);
   } else {
-    __syncthreads();   // the spectrum is read
+    seq_sync<T>();     // the spectrum is read
   }
 #pragma unroll
   for (int e = 0; e < EP; ++e) {
     const int k = j * ep + e;
-    if (e < ep && k < K1) {
-      if (k >= 1 && 2 * k < n) at(2 * k) = make_double2(-im[e].x, -im[e].y);
-      if (2 * k + 1 < n) at(2 * k + 1) = cadd(off, v[e]);
+    if (N || (e < ep && k < K1)) {
+      if (k >= 1) at(2 * k) = make_double2(-im[e].x, -im[e].y);
+      if (N || 2 * k + 1 < n) at(2 * k + 1) = cadd(off, v[e]);
     }
   }
-  __syncthreads();
+  seq_sync<T>();
 }
 
 template <int T>
@@ -271,13 +306,15 @@ struct RowShape {
   static constexpr int PITCH = 9 * T + 1;         // one entry of padding after every 8
 };
 
-// The folded pair into LDS: f(i) the pair's entry i of the transform (1 <= i
-// < n); a thread takes entries jj and n - jj.  Ends with a barrier.
-template <int T, class At, class Get>
-__device__ __forceinline__ void fold_pair(const At& at, int j, int n, const double* sn,
+// The folded pair into LDS: f(base, off) the pair's entry base + off of the
+// transform (off constant); a thread takes entries jj and n - jj.
+template <int T, int N, class Get>
+__device__ __forceinline__ void fold_pair(const Seq& at, int j, int n, const double* sn,
                                           const Get& f) {
+  if (N) n = N;
   j = opaque(j);
   __builtin_assume(j >= 0 && j < T);
+  const int hi = 5 * T - 1 - j;   // N = 8 T: n - jj = hi + T (3 - i)
   double2 a[4], b[4];
   double s[4];
 #pragma unroll
@@ -285,23 +322,23 @@ __device__ __forceinline__ void fold_pair(const At& at, int j, int n, const doub
     const int jj = 1 + j + T * i;
     a[i] = b[i] = make_double2(0.0, 0.0);
     s[i] = 0.0;
-    if (2 * jj <= n) {
+    if (N || 2 * jj <= n) {
       s[i] = sn[jj];
-      a[i] = f(jj);
-      b[i] = f(n - jj);
+      a[i] = f(1 + j, T * i);
+      b[i] = N ? f(hi, T * (3 - i)) : f(n - jj, 0);
     }
   }
   if (j == 0) at(0) = make_double2(0.0, 0.0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int jj = 1 + j + T * i;
-    if (2 * jj <= n) {
+    if (N || 2 * jj <= n) {
       const double2 u = cadd(a[i], b[i]), d = csub(a[i], b[i]);
-      at(jj) = make_double2(s[i] * u.x + 0.5 * d.x, s[i] * u.y + 0.5 * d.y);
-      at(n - jj) = make_double2(s[i] * u.x - 0.5 * d.x, s[i] * u.y - 0.5 * d.y);
+      at.at(1 + j, T * i) = make_double2(s[i] * u.x + 0.5 * d.x, s[i] * u.y + 0.5 * d.y);
+      (N ? at.at(hi, T * (3 - i)) : at(n - jj)) =
+          make_double2(s[i] * u.x - 0.5 * d.x, s[i] * u.y - 0.5 * d.y);
     }
   }
-  __syncthreads();
 }
 
 // Rows in pairs, T threads per pair, 4 T < n <= 8 T (T = 8: n <= 64).
@@ -313,25 +350,26 @@ __global__ __launch_bounds__(RowShape<T>::NT, 4) void k_dst_any_rows(
   __shared__ double2 buf[S::PR][S::PITCH];
   __shared__ double2 wt[S::PR][S::NW];
   const int t = threadIdx.x, pr = t / T, j = t % T, n = P.n;
-  auto at = [&](int i) -> double2& { return buf[pr][i + (i >> 3)]; };
+  const Seq at{buf[pr]};
   const int64_t r = 2 * ((int64_t)blockIdx.x * S::PR + pr);
   const bool la = r < rows, lb = r + 1 < rows;
   {
     const double* fa = in + (la ? r : 0) * ldi - 1;
     const double* fb = in + (lb ? r + 1 : 0) * ldi - 1;
-    fold_pair<T>(at, j, n, P.sn, [&](int i) {
-      return make_double2(la ? fa[i] : 0.0, lb ? fb[i] : 0.0);
+    fold_pair<T, 0>(at, j, n, P.sn, [&](int i, int o) {
+      return make_double2(la ? fa[i + o] : 0.0, lb ? fb[i + o] : 0.0);
     });
   }
-  fft<T>(at, j, P);
-  split_scan<T, 1>(at, j, n, wt[pr]);
+  seq_sync<T>();
+  fft<T, 0>(at, j, P);
+  split_scan<T, 0>(at, j, n, wt[pr]);
   double* oa = out + (la ? r : 0) * ldo - 1;
   double* ob = out + (lb ? r + 1 : 0) * ldo - 1;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int m = 1 + j + T * i;
     if (m < n) {
-      const double2 v = at(m);
+      const double2 v = at.at(1 + j, T * i);
       if (la) oa[m] = scale * v.x;
       if (lb) ob[m] = scale * v.y;
     }
@@ -339,56 +377,72 @@ __global__ __launch_bounds__(RowShape<T>::NT, 4) void k_dst_any_rows(
 }
 
 // Sixteen adjacent columns (eight pairs, 128 bytes of every row) per
-// workgroup, T threads per pair; the pairs lie side by side in LDS, so that
-// every eight lanes access 128 contiguous bytes.
+// workgroup, T threads per pair.  HBM is accessed with the pairs side by side
+// (every eight lanes 128 contiguous bytes of a row), the transforms run with a
+// pair's threads side by side: T <= 64 then needs no barrier between the two
+// accesses.  With FACTOR (two transforms and the factor between them) the
+// vector ALUs were the bound, half of their work the addresses: 3130
+// instructions per wavefront at n = 512, 87 % of the kernel's cycles.  With
+// N = n = 8 T, where every distance is a constant, 1380: 1012 -> 733 us for the
+// z axis of 511^3 (the plain transform of y 490 -> 445); eight columns per
+// workgroup, or the columns in chunks that stay in the last cache, gave nothing more.
 constexpr int kPairs = 8;
-template <int T, bool FACTOR>
+template <int T, bool FACTOR, int N>
 __global__ __launch_bounds__(kPairs * T, 4) void k_dst_columns(DstPlan P, DstColumns A) {
-  constexpr int JW = T * kPairs < 64 ? T : 64 / kPairs;
-  __shared__ double2 buf[8 * T * kPairs];
-  __shared__ double2 wt[kPairs][T / JW];
-  const int t = threadIdx.x, pr = t % kPairs, j = t / kPairs, n = P.n;
-  auto at = [&](int i) -> double2& { return buf[i * kPairs + pr]; };
+  __shared__ double2 buf[kPairs][9 * T + 1];
+  __shared__ double2 wt[kPairs][T > 64 ? T / 64 : 1];
+  const int t = threadIdx.x, n = N ? N : P.n;
   const uint32_t groups = (uint32_t)((A.M + 2 * kPairs - 1) / (2 * kPairs));
   const int64_t bt = blockIdx.x / groups;
-  const int64_t c = ((int64_t)(blockIdx.x - (uint32_t)bt * groups) * kPairs + pr) * 2;
+  const int64_t c0 = (int64_t)(blockIdx.x - (uint32_t)bt * groups) * (2 * kPairs);
+  const int hp = t % kPairs, hj = t / kPairs;   // pair and thread in HBM's order
+  const int64_t c = c0 + 2 * hp;
   const bool la = c < A.M, lb = c + 1 < A.M;
   const int64_t base = bt * A.ldb + (la ? c : 0) - A.ld;
   {
     const double* f = A.in + base;
-    fold_pair<T>(at, j, n, P.sn, [&](int i) {
+    fold_pair<T, N>(Seq{buf[hp]}, hj, n, P.sn, [&](int i, int o) {
       double2 v = make_double2(0.0, 0.0);
-      if (la) v = *reinterpret_cast<const double2*>(f + i * A.ld);
+      if (la) v = *reinterpret_cast<const double2*>(f + (i * A.ld + o * A.ld));
       if (!lb) v.y = 0.0;
       return v;
     });
   }
-  fft<T>(at, j, P);
-  split_scan<T, kPairs>(at, j, n, wt[pr]);
-  if constexpr (FACTOR) {
-    const int64_t ca = la ? c : 0, cb = lb ? c + 1 : ca;
-    const double ya = A.ry[bt * A.ldr + ca], yb = A.ry[bt * A.ldr + cb];
-    const double da = A.ly[bt] + A.mu[ca], db = A.ly[bt] + A.mu[cb];
-    const double* rz = A.rz - A.ldr;
-    const double* lz = A.lz - 1;
-    // (a thread reads and rewrites its own entries jj and n - jj only)
-    fold_pair<T>(at, j, n, P.sn, [&](int m) {
-      double2 v = at(m);
-      v.x *= A.norm * (1.0 - ya * rz[m * A.ldr + ca]) / (lz[m] + da);
-      v.y *= A.norm * (1.0 - yb * rz[m * A.ldr + cb]) / (lz[m] + db);
-      return v;
-    });
-    fft<T>(at, j, P);
-    split_scan<T, kPairs>(at, j, n, wt[pr]);
+  __syncthreads();
+  {
+    const int pr = t / T, j = t % T;
+    const Seq at{buf[pr]};
+    fft<T, N>(at, j, P);
+    split_scan<T, N>(at, j, n, wt[pr]);
+    if constexpr (FACTOR) {
+      const int64_t ca = c0 + 2 * pr < A.M ? c0 + 2 * pr : 0, cb = ca + 1 < A.M ? ca + 1 : ca;
+      const double ya = A.ry[ca * A.ldy + bt], yb = A.ry[cb * A.ldy + bt];
+      const double da = A.ly[bt] + A.mu[ca], db = A.ly[bt] + A.mu[cb];
+      const double* rza = A.rz + ca * A.ldz - 1;
+      const double* rzb = A.rz + cb * A.ldz - 1;
+      const double* lz = A.lz - 1;
+      // (a thread reads and rewrites its own entries jj and n - jj only)
+      fold_pair<T, N>(at, j, n, P.sn, [&](int i, int o) {
+        double2 v = at.at(i, o);
+        v.x *= A.norm * (1.0 - ya * rza[i + o]) / (lz[i + o] + da);
+        v.y *= A.norm * (1.0 - yb * rzb[i + o]) / (lz[i + o] + db);
+        return v;
+      });
+      seq_sync<T>();
+      fft<T, N>(at, j, P);
+      split_scan<T, N>(at, j, n, wt[pr]);
+    }
   }
-  double* o = A.out + base;
+  if constexpr (T <= 64) __syncthreads();
+  const Seq at{buf[hp]};
+  double* o = A.out + base + (1 + hj) * A.ld;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int m = 1 + j + T * i;
+    const int m = 1 + hj + T * i;
     if (m < n && la) {
-      const double2 v = at(m);
-      if (lb) *reinterpret_cast<double2*>(o + m * A.ld) = v;
-      else o[m * A.ld] = v.x;
+      const double2 v = at.at(1 + hj, T * i);
+      if (lb) *reinterpret_cast<double2*>(o + T * i * A.ld) = v;
+      else o[T * i * A.ld] = v.x;
     }
   }
 }
@@ -397,19 +451,15 @@ __global__ __launch_bounds__(256) void k_adi_factors(const double* __restrict__ 
                                                      const int* __restrict__ count, int jmax,
                                                      const double* __restrict__ lam,
                                                      const double* __restrict__ mu, int64_t L,
-                                                     int64_t M, int64_t ldr,
-                                                     double* __restrict__ out) {
+                                                     int64_t M, double* __restrict__ out) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= L * ldr) return;
-  const int64_t l = id / ldr, c = id - l * ldr;
-  double r = 0.0;
-  if (c < M) {
-    const double x = lam[l] + 0.5 * mu[c];
-    r = 1.0;
-    for (int j = 0; j < count[c]; ++j) {
-      const double wj = w[c * jmax + j];
-      r *= (wj - x) / (wj + x);
-    }
+  if (id >= L * M) return;
+  const int64_t c = id / L, l = id - c * L;
+  const double x = lam[l] + 0.5 * mu[c];
+  double r = 1.0;
+  for (int j = 0; j < count[c]; ++j) {
+    const double wj = w[c * jmax + j];
+    r *= (wj - x) / (wj + x);
   }
   out[id] = r;
 }
@@ -441,6 +491,9 @@ hipError_t dst_plan_make(int64_t n, DstPlan& p, double** mem) {
       if (p.np == kDstPasses) return hipErrorInvalidValue;
       p.radix[p.np] = f;
       p.magic[p.np] = (uint32_t)(((uint64_t)1 << 31) / (uint64_t)ns) + 1u;
+      p.ns[p.np] = (int)ns;
+      p.nb[p.np] = (int)(n / f);
+      p.step[p.np] = (int)(n / f / ns);
       ++p.np;
       ns *= f;
       rest /= f;
@@ -490,27 +543,33 @@ hipError_t launch_dst_columns(const DstPlan& p, const DstColumns& a, hipStream_t
   if (g > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)g);
   switch (threads_for(p.n)) {
-#define TDT_COLS(T)                                                                         \
-  case T:                                                                                   \
-    if (a.ry)                                                                               \
-      hipLaunchKernelGGL((k_dst_columns<T, true>), grid, dim3(kPairs * T), 0, st, p, a);    \
-    else                                                                                    \
-      hipLaunchKernelGGL((k_dst_columns<T, false>), grid, dim3(kPairs * T), 0, st, p, a);   \
+#define TDT_COL(T, F, N)                                                                  \
+  hipLaunchKernelGGL((k_dst_columns<T, F, N>), grid, dim3(kPairs * T), 0, st, p, a)
+#define TDT_COLS(T)                                                                       \
+  case T:                                                                                 \
+    if (p.n == 8 * T) {                                                                   \
+      if (a.ry) TDT_COL(T, true, 8 * T);                                                  \
+      else TDT_COL(T, false, 8 * T);                                                      \
+    } else {                                                                              \
+      if (a.ry) TDT_COL(T, true, 0);                                                      \
+      else TDT_COL(T, false, 0);                                                          \
+    }                                                                                     \
     break;
     TDT_COLS(8) TDT_COLS(16) TDT_COLS(32) TDT_COLS(64) TDT_COLS(128)
 #undef TDT_COLS
+#undef TDT_COL
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 hipError_t launch_adi_factors(const double* w, const int* count, int jmax, const double* lam,
-                              const double* mu, int64_t L, int64_t M, int64_t ldr, double* out,
+                              const double* mu, int64_t L, int64_t M, double* out,
                               hipStream_t st) {
-  const int64_t g = (L * ldr + 255) / 256;
+  const int64_t g = (L * M + 255) / 256;
   if (g < 1 || g > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_adi_factors, dim3((unsigned)g), dim3(256), 0, st, w, count, jmax, lam, mu,
-                     L, M, ldr, out);
+                     L, M, out);
   return hipGetLastError();
 }
 

@@ -1049,7 +1049,7 @@ struct tdt_poisson3d_s {
   double* dstmem = nullptr;
   // the iterate in closed form (Ny + 1 and Nz + 1 with small factors): sine
   // transforms along y and z, tables of the ADI cycle's error factors and the
-  // eigenvalues ([mu Nx][ly Ny][lz Nz][ry Ny ldx][rz Nz ldx])
+  // eigenvalues ([mu Nx][ly Ny][lz Nz][ry Nx Ny][rz Nx Nz])
   bool closed = false;
   tdt::DstPlan dsty{}, dstz{};
   double* ymem = nullptr;
@@ -1159,7 +1159,7 @@ constexpr int kAdiCap = 400;
 // Tables of the closed form (see tdt_poisson3d_s::ctab); w_kj and J_k are the
 // handle's schedule.  Blocking.
 tdt_status_t closed_tables(tdt_poisson3d_s* p) {
-  const int64_t nx = p->nx, ny = p->ny, nz = p->nz, ld = p->ldx;
+  const int64_t nx = p->nx, ny = p->ny, nz = p->nz;
   std::vector<double> ev;
   for (int64_t k = 1; k <= nx; ++k) ev.push_back((double)line_eig(nx, p->hx, k));
   for (int64_t k = 1; k <= ny; ++k) ev.push_back((double)line_eig(ny, p->hy, k));
@@ -1169,7 +1169,7 @@ tdt_status_t closed_tables(tdt_poisson3d_s* p) {
   tdt_status_t st = TDT_OK;
   if (tdt::dst_plan_make(ny + 1, p->dsty, &p->ymem) != hipSuccess ||
       tdt::dst_plan_make(nz + 1, p->dstz, &p->zmem) != hipSuccess ||
-      hipMalloc(&p->ctab, (ev.size() + (size_t)((ny + nz) * ld)) * sizeof(double)) != hipSuccess ||
+      hipMalloc(&p->ctab, (ev.size() + (size_t)((ny + nz) * nx)) * sizeof(double)) != hipSuccess ||
       hipMalloc(&w, p->omega.size() * sizeof(double)) != hipSuccess ||
       hipMalloc(&cnt, p->count.size() * sizeof(int)) != hipSuccess)
     st = TDT_ERR_OOM;
@@ -1182,8 +1182,8 @@ tdt_status_t closed_tables(tdt_poisson3d_s* p) {
            hipSuccess ||
        hipMemcpy(cnt, p->count.data(), p->count.size() * sizeof(int), hipMemcpyHostToDevice) !=
            hipSuccess ||
-       tdt::launch_adi_factors(w, cnt, p->jmax, ly, mu, ny, nx, ld, ry, nullptr) != hipSuccess ||
-       tdt::launch_adi_factors(w, cnt, p->jmax, lz, mu, nz, nx, ld, ry + ny * ld, nullptr) !=
+       tdt::launch_adi_factors(w, cnt, p->jmax, ly, mu, ny, nx, ry, nullptr) != hipSuccess ||
+       tdt::launch_adi_factors(w, cnt, p->jmax, lz, mu, nz, nx, ry + ny * nx, nullptr) !=
            hipSuccess ||
        hipDeviceSynchronize() != hipSuccess))
     st = TDT_ERR_HIP;
@@ -1212,8 +1212,9 @@ hipError_t closed_solve(const tdt_poisson3d_s* p, double* v, hipStream_t st) {
   z.ly = z.mu + nx;
   z.lz = z.ly + ny;
   z.ry = z.lz + nz;
-  z.rz = z.ry + ny * ld;
-  z.ldr = ld;
+  z.rz = z.ry + ny * nx;
+  z.ldy = ny;
+  z.ldz = nz;
   z.norm = 2.0 / (double)(ny + 1) * (2.0 / (double)(nz + 1));
   e = tdt::launch_dst_columns(p->dstz, z, st);
   if (e != hipSuccess) return e;

@@ -81,3 +81,25 @@ def test_closed_iterate(dims, eps):
     _check_elementwise(U, ref, _tol(max(counts), _kappa(nx, ny, nz, hx, hy, hz)),
                        f"{dims} eps={eps}")
     assert np.array_equal(U, to_host(s.solve(to_dev(F))))
+
+
+@pytest.mark.parametrize("dims", [(1, 63, 63), (5, 127, 63), (18, 63, 127), (33, 255, 127),
+                                  (3, 127, 255), (2, 511, 255), (17, 255, 511), (1, 1023, 511),
+                                  (16, 63, 1023)])
+def test_closed_iterate_powers_of_two(dims):
+    """Interval counts 8 T of the column transforms' thread counts: 64 (two
+    radix-8 passes), 128 and 256 (a last pass of radix 2 and 4), 512, and 1024
+    (two wavefronts per pair), along y and along z; columns short of a
+    workgroup's sixteen and one more."""
+    tdt = _tdt()
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx * 100 + ny + nz)
+    hx, hy, hz = rng.uniform(0.02, 0.1, 3)
+    F = rng.standard_normal((nz, ny, nx))
+    print(f"[case] closed iterate {dims}", flush=True)
+    s = tdt.Poisson3D(nx, ny, nz, hx, hy, hz, 1e-4)
+    U = to_host(s.solve(to_dev(F)))
+    counts, _ = s.schedule()
+    ref = P3.solve(F, hx, hy, hz, eps=1e-4)
+    _check_elementwise(U, ref, _tol(max(counts), _kappa(nx, ny, nz, hx, hy, hz)), f"{dims}")
+    assert np.array_equal(U, to_host(s.solve(to_dev(F))))
