@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "tdt_dst.h"
+#include "tdt_internal.h"
 
 namespace tdt {
 namespace {
@@ -341,7 +342,7 @@ __device__ __forceinline__ void fold_pair(const Seq& at, int j, int n, const dou
   }
 }
 
-// Rows in pairs, T threads per pair, 4 T < n <= 8 T (T = 8: n <= 64).
+// Rows in pairs, T threads per pair, n <= 8 T.
 template <int T>
 __global__ __launch_bounds__(RowShape<T>::NT, 4) void k_dst_any_rows(
     DstPlan P, const double* __restrict__ in, double* __restrict__ out, int64_t rows, int64_t ldi,
@@ -471,6 +472,19 @@ int threads_for(int64_t n) {
   return t;
 }
 
+// Rows: two or four times as many where that still is at most twelve
+// wavefronts per compute unit.  A few rows are bound by a thread's chain of
+// LDS passes (one pass over 99 x 2000 points 10.5 -> 8.9 us, 499 x 500 11.6 ->
+// 9.4, 999 x 700 15.0 -> 13.1); with more wavefronts the lanes without a
+// butterfly cost more than the shorter chain gives (999 x 3000 22.9 and 22.8
+// us, 999 x 6000 32.9 -> 35.6, 239 x 20000 28.9 -> 30.7).
+int row_threads(int64_t n, int64_t pairs) {
+  int t = threads_for(n);
+  const int most = std::min(t <= 32 ? 4 * t : 2 * t, 1024);
+  while (t < most && pairs * 2 * t <= (int64_t)12 * 64 * device_cus()) t *= 2;
+  return t;
+}
+
 }  // namespace
 
 bool dst_any_supported(int64_t n, int64_t max_n) {
@@ -520,7 +534,7 @@ hipError_t dst_plan_make(int64_t n, DstPlan& p, double** mem) {
 
 hipError_t launch_dst_any_rows(const DstPlan& p, const double* in, double* out, int64_t rows,
                                int64_t ldi, int64_t ldo, double scale, hipStream_t st) {
-  switch (threads_for(p.n)) {
+  switch (row_threads(p.n, (rows + 1) / 2)) {
 #define TDT_ROWS(T)                                                                         \
   case T: {                                                                                 \
     const int64_t g = ((rows + 1) / 2 + RowShape<T>::PR - 1) / RowShape<T>::PR;             \

@@ -103,3 +103,17 @@ def test_closed_iterate_powers_of_two(dims):
     ref = P3.solve(F, hx, hy, hz, eps=1e-4)
     _check_elementwise(U, ref, _tol(max(counts), _kappa(nx, ny, nz, hx, hy, hz)), f"{dims}")
     assert np.array_equal(U, to_host(s.solve(to_dev(F))))
+
+
+@pytest.mark.parametrize("n,ny", [(60, 24603), (120, 12303), (250, 6202), (500, 3101), (1000, 1602),
+                                  (2000, 801), (4095, 402)])
+def test_dst_rows_many(n, ny):
+    """Enough rows for the fewest threads per pair (few rows take two or four
+    times as many: test_dst_rows)."""
+    tdt = _tdt()
+    rng = np.random.default_rng(n)
+    hx, hy = rng.uniform(0.002, 0.2, 2)
+    print(f"[case] dst rows n={n} ny={ny}", flush=True)
+    F = rng.standard_normal((ny, n - 1))
+    U = to_host(tdt.Poisson2D(n - 1, ny, hx, hy).solve(to_dev(F)))
+    assert oracle.rel_err(U, P2.solve(F, hx, hy)) <= tol2(n - 1, ny, hx, hy)
