@@ -1230,7 +1230,10 @@ tdt_status_t build_general_dir(tdt_plan_s* p, int dir, double& dom, double& kap)
   std::vector<double> tK((size_t)P * 4);
   // the tiles' Green rows (the first pass's summaries are their dot
   // products with the tile's F) and their supports: with several tiles the
-  // first pass reads the widest supports over the tiles
+  // first pass reads the widest supports over the tiles.  A float plan with a
+  // ragged last tile keeps its float sweeps: the supports' double sums move
+  // single floats of X next to the tiles' edges, and with them the double
+  // entry gradients by 1e-9 (9313 rows x 11).
   std::vector<double> green(P > 1 ? (size_t)P * 2 * L : 0);
   int64_t kfmax = 0, klmax = 0;
   for (int64_t t = 0; !green.empty() && t < P; ++t) {
@@ -1245,7 +1248,8 @@ tdt_status_t build_general_dir(tdt_plan_s* p, int dir, double& dom, double& kap)
     klmax = std::max(klmax, kl);
   }
   int gkf = 0, gkl = 0;
-  if (!green.empty()) green_support_rounded(L, kfmax, klmax, gkf, gkl);
+  if (!green.empty() && (sizeof(Tc) == 8 || N % L == 0))
+    green_support_rounded(L, kfmax, klmax, gkf, gkl);
   p->gen_kf[dir] = gkf;
   p->gen_kl[dir] = gkl;
   if (gkf > 0) {
