@@ -69,6 +69,7 @@ SOURCES_TILES = ("paper_1002_2469_amd/csrc/tdt_kernels.hip", "paper_1002_2469_am
                  "paper_1002_2469_amd/csrc/tdt_api.cpp")
 SOURCES_POISSON = ("paper_1002_2469_amd/csrc/tdt_poisson.hip", "paper_1002_2469_amd/csrc/tdt_strided.hip",
                    "paper_1002_2469_amd/csrc/tdt_dst.hip", "paper_1002_2469_amd/csrc/tdt_dst.h",
+                   "paper_1002_2469_amd/csrc/tdt_dst_dense.hip",
                    "paper_1002_2469_amd/csrc/tdt_strided.h", "paper_1002_2469_amd/csrc/tdt_internal.h",
                    "paper_1002_2469_amd/csrc/tdt_api.cpp")
 

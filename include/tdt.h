@@ -192,8 +192,8 @@ tdt_status_t tdt_solve_strided(tdt_plan_t plan, const double *F, double *X, int6
  * on Nx x Ny interior points with u = 0 on the boundary.  A sine transform
  * along x (a real FFT of length Nx+1 of each folded row, then a prefix sum
  * for the odd coefficients: in one kernel when Nx+1 is a power of two from
- * 128 to 8192, or any number up to 8192 whose prime factors are at most 13,
- * through hipFFT otherwise) leaves one tridiagonal Toeplitz
+ * 128 to 8192, any number up to 8192 whose prime factors are at most 13, or
+ * any number up to 512 (a matrix product), through hipFFT otherwise) leaves one tridiagonal Toeplitz
  * system per mode k along y, t_+-1 = -1,
  * t_0 = 2 + hy^2 (4/hx^2) sin^2(pi k / (2 (Nx+1))); the inverse transform
  * gives U.  With the one-kernel transform and TDT_F64 (and, unless Nx+1 is a
@@ -257,8 +257,8 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p);
  * full cycle, d_J^2 with d_J = prod_j (w_j - a)/(w_j + a), is <= eps, so the
  * 2-norm error of the result relative to the exact discrete solution is at
  * most eps (plus rounding).  J_k falls as k grows.  Where Nx+1 has a
- * one-kernel transform and Ny+1 and Nz+1 are at most 1024 with prime factors
- * at most 13, the iterate is evaluated in closed form instead: both
+ * one-kernel transform and Ny+1 and Nz+1 are at most 512, or up to 1024 with
+ * prime factors at most 13, the iterate is evaluated in closed form instead: both
  * directions' operators commute and are diagonal in the sine basis of the
  * plane, where the J_k steps from 0 leave
  *   v = (1 - prod_j r_j(ly + mu_k/2) r_j(lz + mu_k/2)) fhat / (ly + lz + mu_k),
@@ -267,8 +267,9 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p);
  * pass each) around that factor.  The same iterate up to rounding.
  * 1 <= Ny, Nz <= 2^24
  * (lines of more than 1024 points are solved in tiles of 512, as by
- * tdt_solve_strided), 640 Nxp Ny < 2^31 with Nxp = 16 ceil(Nx/16) + 16 on
- * the fused path, Nx otherwise (31-bit byte offsets of the z lines),
+ * tdt_solve_strided), 640 Nxp Ny < 2^31 with Nxp = 16 ceil(Nx/16) + 16 where
+ * Nx+1 is a power of two from 128 to 8192, Nx otherwise (31-bit byte offsets
+ * of the z lines),
  * 0 < eps < 1; a count above 400 for some mode -> TDT_ERR_INVALID_ARG.  The
  * handle owns the per-iteration tables (~(38 + 4 ceil(N/16)) doubles per
  * mode and iteration, about twice that for tiled lines), for tiled lines

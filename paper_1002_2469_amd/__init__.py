@@ -489,7 +489,7 @@ class Poisson3D:
     on the device.  Sine transform along x, Peaceman-Rachford ADI on every
     mode's (y, z) plane with the optimal parameters (strided line solves
     along y and z, or the same iterate in closed form through sine transforms
-    along y and z where Ny + 1 and Nz + 1 have small factors), inverse
+    along y and z where Ny + 1 and Nz + 1 are at most 512 or, up to 1024, have small factors), inverse
     transform.  eps bounds the ADI error
     relative to the exact discrete solution (2-norm)."""
 

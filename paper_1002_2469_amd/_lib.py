@@ -16,7 +16,8 @@ _ROOT = os.path.dirname(_HERE)
 LIB_PATH = os.path.join(_HERE, "libtdt.so")
 SOURCES = [os.path.join(_HERE, "csrc", "tdt_kernels.hip"), os.path.join(_HERE, "csrc", "tdt_api.cpp"),
            os.path.join(_HERE, "csrc", "tdt_poisson.hip"), os.path.join(_HERE, "csrc", "tdt_strided.hip"),
-           os.path.join(_HERE, "csrc", "tdt_short.hip"), os.path.join(_HERE, "csrc", "tdt_dst.hip")]
+           os.path.join(_HERE, "csrc", "tdt_short.hip"), os.path.join(_HERE, "csrc", "tdt_dst.hip"),
+           os.path.join(_HERE, "csrc", "tdt_dst_dense.hip")]
 HEADER = os.path.join(_ROOT, "include", "tdt.h")
 
 # status codes (include/tdt.h)

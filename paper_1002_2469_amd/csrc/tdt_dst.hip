@@ -452,7 +452,8 @@ __global__ __launch_bounds__(256) void k_adi_factors(const double* __restrict__ 
                                                      const int* __restrict__ count, int jmax,
                                                      const double* __restrict__ lam,
                                                      const double* __restrict__ mu, int64_t L,
-                                                     int64_t M, double* __restrict__ out) {
+                                                     int64_t M, bool modes_last,
+                                                     double* __restrict__ out) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (id >= L * M) return;
   const int64_t c = id / L, l = id - c * L;
@@ -462,7 +463,7 @@ __global__ __launch_bounds__(256) void k_adi_factors(const double* __restrict__ 
     const double wj = w[c * jmax + j];
     r *= (wj - x) / (wj + x);
   }
-  out[id] = r;
+  out[modes_last ? l * M + c : id] = r;
 }
 
 // Threads per pair: the least power of two with n <= 8 T, at least 8.
@@ -487,17 +488,34 @@ int row_threads(int64_t n, int64_t pairs) {
 
 }  // namespace
 
-bool dst_any_supported(int64_t n, int64_t max_n) {
-  if (n < 2 || n > max_n) return false;
+namespace {
+bool small_factors(int64_t n) {
   for (int f : {2, 3, 5, 7, 11, 13})
     while (n % f == 0) n /= f;
   return n == 1;
+}
+}  // namespace
+
+bool dst_any_supported(int64_t n, int64_t max_n) {
+  return n >= 2 && n <= max_n && (n <= kDstDenseMax || small_factors(n));
 }
 
 hipError_t dst_plan_make(int64_t n, DstPlan& p, double** mem) {
   *mem = nullptr;
   p = DstPlan{};
   p.n = (int)n;
+  if (!small_factors(n)) {
+    if (n > kDstDenseMax) return hipErrorInvalidValue;
+    std::vector<double> tab;
+    dst_dense_table(n, tab);
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(mem), tab.size() * sizeof(double));
+    if (e != hipSuccess) {
+      *mem = nullptr;
+      return e;
+    }
+    p.tw = *mem;
+    return hipMemcpy(*mem, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice);
+  }
   // the large radices first: their first pass has no twiddles
   int64_t rest = n, ns = 1;
   for (int f : {8, 4, 2, 13, 11, 7, 5, 3})
@@ -534,6 +552,7 @@ hipError_t dst_plan_make(int64_t n, DstPlan& p, double** mem) {
 
 hipError_t launch_dst_any_rows(const DstPlan& p, const double* in, double* out, int64_t rows,
                                int64_t ldi, int64_t ldo, double scale, hipStream_t st) {
+  if (p.np == 0) return launch_dst_dense_rows(p, in, out, rows, ldi, ldo, scale, st);
   switch (row_threads(p.n, (rows + 1) / 2)) {
 #define TDT_ROWS(T)                                                                         \
   case T: {                                                                                 \
@@ -552,6 +571,7 @@ hipError_t launch_dst_any_rows(const DstPlan& p, const double* in, double* out, 
 }
 
 hipError_t launch_dst_columns(const DstPlan& p, const DstColumns& a, hipStream_t st) {
+  if (p.np == 0) return launch_dst_dense_columns(p, a, st);
   if (a.M < 1 || a.nb < 1 || (a.ld & 1) || (a.ldb & 1)) return hipErrorInvalidValue;
   const int64_t g = (a.M + 2 * kPairs - 1) / (2 * kPairs) * a.nb;
   if (g > 0x7fffffff) return hipErrorInvalidValue;
@@ -578,12 +598,12 @@ hipError_t launch_dst_columns(const DstPlan& p, const DstColumns& a, hipStream_t
 }
 
 hipError_t launch_adi_factors(const double* w, const int* count, int jmax, const double* lam,
-                              const double* mu, int64_t L, int64_t M, double* out,
-                              hipStream_t st) {
+                              const double* mu, int64_t L, int64_t M, bool modes_last,
+                              double* out, hipStream_t st) {
   const int64_t g = (L * M + 255) / 256;
   if (g < 1 || g > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_adi_factors, dim3((unsigned)g), dim3(256), 0, st, w, count, jmax, lam, mu,
-                     L, M, out);
+                     L, M, modes_last, out);
   return hipGetLastError();
 }
 

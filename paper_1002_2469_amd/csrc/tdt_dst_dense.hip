@@ -10,10 +10,17 @@
 // and factor are one pass over HBM; its eight wavefronts share the 16-row
 // tiles of the matrix, whose entries come from L2 in the order of the lanes.
 //
-// Bound by the matrix units from n of about 150 on (n flops per entry), by HBM
-// below.  Where there are at least two workgroups per compute unit, 32
-// sequences share each load of the matrix (CT = 2); below, 16 (more
-// workgroups).
+// Bound by the matrix units from n of about 150 on (n flops per entry; the rows
+// of 300^3 points, n = 301: 8.1 GFLOP in 216 us, 38 TFLOP/s), by HBM below
+// (50 x 100000 points, 80 MB, 44 us), by launches when small.  Before, a
+// library FFT between fold, split and prefix-sum kernels, transposes around
+// the 2D line solves and the iterated 3D half-steps: 2D 50 x 1000 points 42 ->
+// 20 us, 250 x 20000 378 -> 148, 508 x 60000 2280 -> 1118; 3D 40 x 50 x 59 604 ->
+// 29, 100^3 781 -> 61, 300^3 6905 -> 1448.  Above 512 the matrix outgrows both the
+// work saved and the LDS.  Where there are at least two workgroups per compute
+// unit, 32 sequences share each load of the matrix (CT = 2); below, 16 (more
+// workgroups), and a few rows' tiles are dealt to several workgroups (508 x 500
+// points 97 -> 35 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -33,13 +40,14 @@ constexpr int kDenseNT = 512;
 __host__ __device__ inline int dense_tiles(int n, int even) { return ((even ? (n - 1) / 2 : n / 2) + 15) / 16; }
 __host__ __device__ inline int dense_steps(int n, int even) { return ((even ? (n - 1) / 2 : n / 2) + 3) / 4; }
 
-// The products of one wavefront: tiles w, w + 8, ... (the odd half's first).
+// The products of one wavefront: tiles w, w + step, ... (the odd half's first).
 // get(k, h): entry k (1-based position in the folded sequence) of the lane's
 // sequence h; TABLE_A: the matrix is the left operand (columns of an array),
 // else the right one (rows).
 template <int TPW, int CT, bool TABLE_A, class Get>
 __device__ __forceinline__ void dense_products(const double* __restrict__ tab, int n, int w,
-                                               int lane, const Get& get, f64x4 (&acc)[TPW][CT]) {
+                                               int step, int lane, const Get& get,
+                                               f64x4 (&acc)[TPW][CT]) {
   const int to = dense_tiles(n, 0), te = dense_tiles(n, 1);
   const int ko = dense_steps(n, 0), ke = dense_steps(n, 1);
   const int kq = lane / 16;
@@ -47,7 +55,7 @@ __device__ __forceinline__ void dense_products(const double* __restrict__ tab, i
   for (int q = 0; q < TPW; ++q) {
 #pragma unroll
     for (int h = 0; h < CT; ++h) acc[q][h] = f64x4{0.0, 0.0, 0.0, 0.0};
-    const int tile = w + 8 * q;   // uniform in the wavefront
+    const int tile = w + step * q;   // uniform in the wavefront
     if (tile >= to + te) continue;
     const bool even = tile >= to;
     const int ks = even ? ke : ko;
@@ -56,16 +64,43 @@ __device__ __forceinline__ void dense_products(const double* __restrict__ tab, i
     // s_i at position i, d_i at n - i; steps past the last entry meet zeros of
     // the matrix (and positions inside the sequence, n >= 17)
     const int p0 = even ? n - 1 - kq : 1 + kq, dp = even ? -4 : 4;
+    if constexpr (TPW == 1) {
 #pragma unroll 8
-    for (int s = 0; s < ks; ++s) {
-      const double a = tb[s * 64];
-      const int pos = p0 + dp * s;
+      for (int s = 0; s < ks; ++s) {
+        const double a = tb[s * 64];
 #pragma unroll
-      for (int h = 0; h < CT; ++h) {
-        const double b = get(pos, h);
-        acc[q][h] = TABLE_A ? __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[q][h], 0, 0, 0)
-                            : __builtin_amdgcn_mfma_f64_16x16x4f64(b, a, acc[q][h], 0, 0, 0);
+        for (int h = 0; h < CT; ++h) {
+          const double b = get(p0 + dp * s, h);
+          acc[q][h] = TABLE_A ? __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[q][h], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f64_16x16x4f64(b, a, acc[q][h], 0, 0, 0);
+        }
       }
+      continue;
+    }
+    // Eight steps' matrix entries are requested while the eight before are
+    // used: with one or two workgroups per compute unit their latency was the
+    // bound (300^3 rows 455 -> 216 us).  Short sequences (TPW = 1) have more
+    // workgroups, and lose some to the registers (100^3 solve 60 -> 68 us).
+    constexpr int U = 8;
+    double a[U], an[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = tb[min(u, ks - 1) * 64];
+    for (int s0 = 0; s0 < ks; s0 += U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) an[u] = tb[min(s0 + U + u, ks - 1) * 64];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (s0 + u >= ks) break;
+        const int pos = p0 + dp * (s0 + u);
+#pragma unroll
+        for (int h = 0; h < CT; ++h) {
+          const double b = get(pos, h);
+          acc[q][h] = TABLE_A ? __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b, acc[q][h], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f64_16x16x4f64(b, a[u], acc[q][h], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) a[u] = an[u];
     }
   }
 }
@@ -80,7 +115,7 @@ __device__ __forceinline__ int dense_coef(int n, int tile, int e) {
 template <int NMAX, int CT, bool FACTOR>
 __global__ __launch_bounds__(kDenseNT, 2) void k_dst_dense_columns(const double* __restrict__ tab,
                                                                 int n, DstColumns A) {
-  constexpr int C = 16 * CT, TPW = NMAX / 128, RS = kDenseNT / C;
+  constexpr int C = 16 * CT, TPW = (NMAX + 127) / 128, RS = kDenseNT / C;
   __shared__ double buf[NMAX * C];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   // position p of column c; odd positions of 32 columns swap their halves
@@ -120,7 +155,7 @@ __global__ __launch_bounds__(kDenseNT, 2) void k_dst_dense_columns(const double*
   __syncthreads();
   f64x4 acc[TPW][CT];
   auto get = [&](int p, int h) { return at(p, 16 * h + (lane & 15)); };
-  dense_products<TPW, CT, true>(tab, n, w, lane, get, acc);
+  dense_products<TPW, CT, true>(tab, n, w, 8, lane, get, acc);
   // the lane's entries: coefficient row 4 v + lane / 16 of a tile, column
   // 16 h + lane % 16
   if constexpr (FACTOR) {
@@ -147,7 +182,7 @@ __global__ __launch_bounds__(kDenseNT, 2) void k_dst_dense_columns(const double*
       at(n - i, hc) = a - b;
     }
     __syncthreads();
-    dense_products<TPW, CT, true>(tab, n, w, lane, get, acc);
+    dense_products<TPW, CT, true>(tab, n, w, 8, lane, get, acc);
   }
 #pragma unroll
   for (int h = 0; h < CT; ++h) {
@@ -164,17 +199,20 @@ __global__ __launch_bounds__(kDenseNT, 2) void k_dst_dense_columns(const double*
   }
 }
 
-// Rows, 16 CT per workgroup; a pitch of 2 mod 32 doubles: 16 rows of 2
-// positions without bank conflicts.
+// Rows, 16 CT per workgroup, the tiles dealt to `parts` workgroups (few rows:
+// in and out are different arrays).  A pitch of twice an odd number: 16 rows
+// of 2 positions without bank conflicts.
 template <int NMAX, int CT>
 __global__ __launch_bounds__(kDenseNT, 2) void k_dst_dense_rows(const double* __restrict__ tab, int n,
                                                              const double* __restrict__ in,
                                                              double* __restrict__ out, int64_t rows,
-                                                             int64_t ldi, int64_t ldo, double scale) {
-  constexpr int R = 16 * CT, TPW = NMAX / 128, PITCH = NMAX + 2;
+                                                             int64_t ldi, int64_t ldo, double scale,
+                                                             int parts) {
+  constexpr int R = 16 * CT, TPW = (NMAX + 127) / 128, PITCH = NMAX == 320 ? 318 : NMAX + 2;
   __shared__ double buf[R * PITCH];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int64_t r0 = (int64_t)blockIdx.x * R;
+  const int64_t r0 = (int64_t)(blockIdx.x / parts) * R;
+  const int w0 = w + 8 * (int)(blockIdx.x % parts);
   for (int i = 1 + lane; i <= n / 2; i += 64) {
     double a[R / 8], b[R / 8];
 #pragma unroll
@@ -197,12 +235,12 @@ __global__ __launch_bounds__(kDenseNT, 2) void k_dst_dense_rows(const double* __
   __syncthreads();
   f64x4 acc[TPW][CT];
   dense_products<TPW, CT, false>(
-      tab, n, w, lane,
+      tab, n, w0, 8 * parts, lane,
       [&](int p, int h) { return buf[(16 * h + (lane & 15)) * PITCH + p - 1]; }, acc);
   // the lane's entries: row 16 h + 4 v + lane / 16, coefficient lane % 16
 #pragma unroll
   for (int q = 0; q < TPW; ++q) {
-    const int m = dense_coef(n, w + 8 * q, lane & 15);
+    const int m = dense_coef(n, w0 + 8 * parts * q, lane & 15);
     if (m >= n) continue;
 #pragma unroll
     for (int h = 0; h < CT; ++h)
@@ -218,8 +256,11 @@ template <int NMAX, int CT>
 void dense_rows(const DstPlan& p, const double* in, double* out, int64_t rows, int64_t ldi,
                 int64_t ldo, double scale, hipStream_t st) {
   const int64_t g = (rows + 16 * CT - 1) / (16 * CT);
-  hipLaunchKernelGGL((k_dst_dense_rows<NMAX, CT>), dim3((unsigned)g), dim3(kDenseNT), 0, st, p.tw,
-                     p.n, in, out, rows, ldi, ldo, scale);
+  const int tiles = dense_tiles(p.n, 0) + dense_tiles(p.n, 1);
+  int parts = 1;
+  while (g * 2 * parts <= device_cus() && 8 * parts < tiles) parts *= 2;
+  hipLaunchKernelGGL((k_dst_dense_rows<NMAX, CT>), dim3((unsigned)(g * parts)), dim3(kDenseNT), 0,
+                     st, p.tw, p.n, in, out, rows, ldi, ldo, scale, parts);
 }
 
 template <int NMAX, int CT>
@@ -237,6 +278,9 @@ void dense_columns(const DstPlan& p, const DstColumns& a, hipStream_t st) {
 
 void dst_dense_table(int64_t n, std::vector<double>& tab) {
   const long double pi = 3.141592653589793238462643383279502884L;
+  std::vector<double> sn((size_t)(2 * n));   // sin(pi q / n)
+  for (int64_t q = 0; q < 2 * n; ++q)
+    sn[(size_t)q] = (double)std::sin(pi * (long double)q / (long double)n);
   tab.clear();
   for (int even = 0; even < 2; ++even) {
     const int K = even ? (int)(n - 1) / 2 : (int)n / 2;
@@ -245,9 +289,7 @@ void dst_dense_table(int64_t n, std::vector<double>& tab) {
       for (int s = 0; s < steps; ++s)
         for (int l = 0; l < 64; ++l) {
           const int64_t m = 2 * (16 * t + l % 16) + 1 + even, i = 4 * s + l / 16 + 1;
-          const int64_t q = i * m % (2 * n);
-          tab.push_back(m < n && i <= K ? (double)std::sin(pi * (long double)q / (long double)n)
-                                        : 0.0);
+          tab.push_back(m < n && i <= K ? sn[(size_t)(i * m % (2 * n))] : 0.0);
         }
   }
 }
@@ -262,6 +304,7 @@ hipError_t launch_dst_dense_rows(const DstPlan& p, const double* in, double* out
   else dense_rows<N, 1>(p, in, out, rows, ldi, ldo, scale, st)
   if (p.n <= 128) { TDT_DENSE(128); }
   else if (p.n <= 256) { TDT_DENSE(256); }
+  else if (p.n < 320) { TDT_DENSE(320); }   // two workgroups' LDS per compute unit
   else { TDT_DENSE(512); }
 #undef TDT_DENSE
   return hipGetLastError();
@@ -277,6 +320,7 @@ hipError_t launch_dst_dense_columns(const DstPlan& p, const DstColumns& a, hipSt
   else dense_columns<N, 1>(p, a, st)
   if (p.n <= 128) { TDT_DENSE(128); }
   else if (p.n <= 256) { TDT_DENSE(256); }
+  else if (p.n < 320) { TDT_DENSE(320); }   // two workgroups' LDS per compute unit
   else { TDT_DENSE(512); }
 #undef TDT_DENSE
   return hipGetLastError();

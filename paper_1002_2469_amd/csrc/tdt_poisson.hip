@@ -17,8 +17,8 @@
 // Trans. ASSP 28, 1980): with Y_k = sum_j y_j e^{-2 pi i j k / n},
 //     S_{2k} = -Im Y_k,   S_1 = Re Y_0 / 2,   S_{2k+1} = S_{2k-1} + Re Y_k,
 // the odd coefficients a prefix sum along k.  One kernel does all of it where
-// Nx + 1 is a power of two (k_dst_rows) or has small factors (tdt_dst.hip);
-// otherwise the FFTs are hipFFT's between this library's fold and prefix-sum
+// Nx + 1 is a power of two (k_dst_rows), has small factors (tdt_dst.hip) or is
+// at most 512 (tdt_dst_dense.hip); otherwise the FFTs are hipFFT's between this library's fold and prefix-sum
 // kernels.
 #include <hip/hip_runtime.h>
 #include <hipfft/hipfft.h>
@@ -50,7 +50,7 @@ struct tdt_poisson_s {
   bool fused = false;            // Nx + 1 = 2 N2 (N2 a power of two): k_dst_rows
   double* tw = nullptr;          // its twiddle tables
   double* pw = nullptr;
-  bool any = false;              // else Nx + 1 has small factors: k_dst_any_rows
+  bool any = false;              // else Nx + 1 has small factors or is small: tdt_dst.h
   tdt::DstPlan dst{};
   double* dstmem = nullptr;      // its tables
   bool profile = false;
@@ -1019,11 +1019,11 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p) {
 //
 // A1 and A2 commute and share the sine basis of the plane, in which the cycle
 // from v = 0 multiplies fhat by (1 - rho(ly) rho(lz)) / (ly + lz + mu_k),
-// rho(l) = prod_j (w_j - l - mu_k/2) / (w_j + l + mu_k/2).  Where Ny + 1 and
-// Nz + 1 have small factors the iterate is formed from that (closed_solve):
+// rho(l) = prod_j (w_j - l - mu_k/2) / (w_j + l + mu_k/2).  Where the sine
+// transforms take Ny + 1 and Nz + 1 (tdt_dst.h) the iterate is formed from that (closed_solve):
 // three passes over the array (transform along y; along z, the factor, and
 // back; back along y), 48 bytes per unknown, instead of 40 per iteration and
-// about 12 iterations: 511^3 14.65 -> 2.80 ms, error against the exact
+// about 12 iterations: 511^3 14.65 -> 2.51 ms, error against the exact
 // solution 4e-13 -> 5e-14.  (Chunks of modes small enough for the Infinity
 // Cache did not help the iteration: 14.2 ms at best, its half-steps being as
 // slow from cache.)
@@ -1044,10 +1044,10 @@ struct tdt_poisson3d_s {
   double* Yt = nullptr;     // lines of more than 1024 rows: the tiles' end values
   double* Gt = nullptr;     // and outside values, [nb][K][2][modes] each
   double* fh = nullptr;     // fhat (U otherwise)
-  bool any = false;         // Nx + 1 with small factors: k_dst_any_rows
+  bool any = false;         // else Nx + 1 with small factors or small: tdt_dst.h
   tdt::DstPlan dst{};
   double* dstmem = nullptr;
-  // the iterate in closed form (Ny + 1 and Nz + 1 with small factors): sine
+  // the iterate in closed form (Ny + 1 and Nz + 1 that dst_plan_make takes): sine
   // transforms along y and z, tables of the ADI cycle's error factors and the
   // eigenvalues ([mu Nx][ly Ny][lz Nz][ry Nx Ny][rz Nx Nz])
   bool closed = false;
@@ -1182,9 +1182,9 @@ tdt_status_t closed_tables(tdt_poisson3d_s* p) {
            hipSuccess ||
        hipMemcpy(cnt, p->count.data(), p->count.size() * sizeof(int), hipMemcpyHostToDevice) !=
            hipSuccess ||
-       tdt::launch_adi_factors(w, cnt, p->jmax, ly, mu, ny, nx, ry, nullptr) != hipSuccess ||
-       tdt::launch_adi_factors(w, cnt, p->jmax, lz, mu, nz, nx, ry + ny * nx, nullptr) !=
-           hipSuccess ||
+       tdt::launch_adi_factors(w, cnt, p->jmax, ly, mu, ny, nx, false, ry, nullptr) != hipSuccess ||
+       tdt::launch_adi_factors(w, cnt, p->jmax, lz, mu, nz, nx, p->dstz.np == 0, ry + ny * nx,
+                               nullptr) != hipSuccess ||
        hipDeviceSynchronize() != hipSuccess))
     st = TDT_ERR_HIP;
   (void)hipFree(w);
@@ -1214,7 +1214,7 @@ hipError_t closed_solve(const tdt_poisson3d_s* p, double* v, hipStream_t st) {
   z.ry = z.lz + nz;
   z.rz = z.ry + ny * nx;
   z.ldy = ny;
-  z.ldz = nz;
+  z.ldz = p->dstz.np == 0 ? nx : nz;
   z.norm = 2.0 / (double)(ny + 1) * (2.0 / (double)(nz + 1));
   e = tdt::launch_dst_columns(p->dstz, z, st);
   if (e != hipSuccess) return e;
@@ -1292,6 +1292,13 @@ tdt_status_t tdt_poisson3d_create(int64_t nx, int64_t ny, int64_t nz, double hx,
   p->any = !p->fused && tdt::dst_any_supported(n, tdt::kDstAnyMax);
   p->closed = (p->fused || p->any) && tdt::dst_any_supported(ny + 1, tdt::kDstColMax) &&
               tdt::dst_any_supported(nz + 1, tdt::kDstColMax);
+  // (31-bit byte offsets of the iteration's z lines; the columns of the closed
+  // form have none)
+  auto lines_fit = [&](int64_t ld) {
+    return (int64_t)(5 * tdt::kStrB) * ld * ny * 8 + 512 < ((int64_t)1 << 31);
+  };
+  // unpadded rows on the hipFFT path where padded ones are out of its reach
+  if (p->any && !p->closed && !lines_fit(padded_row(nx))) p->any = false;
   // tables of every half-step: classes k < K_j with t_+-1 = -1,
   // t_0 = 2 + h^2 (w_kj + mu_k / 2), and the epilogue of the step
   std::vector<double> tab;
@@ -1343,8 +1350,7 @@ tdt_status_t tdt_poisson3d_create(int64_t nx, int64_t ny, int64_t nz, double hx,
   // 511-double rows, 17.1 ms with 512 and 16.9 ms with 528)
   const bool one = p->fused || p->any;
   p->ldx = one ? padded_row(nx) : nx;
-  if (st == TDT_OK && (int64_t)(5 * tdt::kStrB) * p->ldx * ny * 8 + 512 >= ((int64_t)1 << 31))
-    st = TDT_ERR_INVALID_ARG;
+  if (st == TDT_OK && !(p->closed && p->any) && !lines_fit(p->ldx)) st = TDT_ERR_INVALID_ARG;
   if (st == TDT_OK &&
       (hipMalloc(&p->sn, (size_t)n * sizeof(double)) != hipSuccess ||
        (one && !p->closed &&

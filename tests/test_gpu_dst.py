@@ -117,3 +117,65 @@ def test_dst_rows_many(n, ny):
     F = rng.standard_normal((ny, n - 1))
     U = to_host(tdt.Poisson2D(n - 1, ny, hx, hy).solve(to_dev(F)))
     assert oracle.rel_err(U, P2.solve(F, hx, hy)) <= tol2(n - 1, ny, hx, hy)
+
+
+@pytest.mark.parametrize("n", [17, 19, 51, 97, 127, 129, 131, 241, 254, 257, 262, 318, 323, 383, 502, 509, 521])
+def test_dst_dense_rows(n):
+    """Interval counts with a prime factor above 13: the matrix form up to 512
+    (the edges of its LDS sizes: 127 | 129, 254 | 257, 318 | 323; odd and even),
+    few rows (16 per workgroup) and many (32), ragged; 521: hipFFT."""
+    tdt = _tdt()
+    rng = np.random.default_rng(n)
+    hx, hy = rng.uniform(0.002, 0.2, 2)
+    for ny in (1, 37, 16389 if n <= 129 else 450):
+        print(f"[case] dense rows n={n} ny={ny}", flush=True)
+        F = rng.standard_normal((ny, n - 1))
+        U = to_host(tdt.Poisson2D(n - 1, ny, hx, hy).solve(to_dev(F)))
+        err = oracle.rel_err(U, P2.solve(F, hx, hy))
+        assert err <= tol2(n - 1, ny, hx, hy), (n, ny, err)
+
+
+@pytest.mark.parametrize("dims", [(1, 16, 18), (15, 50, 16), (33, 18, 60), (16, 127, 130),
+                                  (50, 128, 33), (17, 256, 50), (3, 50, 261), (5, 382, 22),
+                                  (2, 63, 508), (40, 508, 15), (33, 600, 37), (3, 16, 521),
+                                  (400, 16, 82), (400, 82, 16), (64, 259, 130), (64, 259, 282),
+                                  (64, 282, 259)])
+@pytest.mark.parametrize("eps", [0.3, 1e-13])
+def test_dense_iterate(dims, eps):
+    """The matrix form along y, along z with the factors, or both, next to the
+    FFT form; 16 and 32 columns per workgroup, ragged; (3, 16, 521) iterates."""
+    tdt = _tdt()
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx * 100 + ny + nz)
+    hx, hy, hz = rng.uniform(0.02, 0.1, 3)
+    F = rng.standard_normal((nz, ny, nx))
+    print(f"[case] dense iterate {dims} eps={eps}", flush=True)
+    s = tdt.Poisson3D(nx, ny, nz, hx, hy, hz, eps)
+    U = to_host(s.solve(to_dev(F)))
+    counts, _ = s.schedule()
+    ref = P3.solve(F, hx, hy, hz, eps=eps)
+    _check_elementwise(U, ref, _tol(max(counts), _kappa(nx, ny, nz, hx, hy, hz)),
+                       f"{dims} eps={eps}")
+    assert np.array_equal(U, to_host(s.solve(to_dev(F))))
+
+
+@pytest.mark.parametrize("dims", [(17, 190000, 1), (18, 180000, 1)])
+def test_padded_rows_out_of_reach(dims):
+    """Padded rows would pass the line solves' 31-bit offsets, the unpadded
+    ones do not: hipFFT (iterated)."""
+    tdt = _tdt()
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx)
+    F = rng.standard_normal((nz, ny, nx))
+    print(f"[case] padded rows {dims}", flush=True)
+    s = tdt.Poisson3D(nx, ny, nz, 0.05, 0.06, 0.07, 0.3)
+    U = to_host(s.solve(to_dev(F)))
+    counts, _ = s.schedule()
+    ref = P3.solve(F, 0.05, 0.06, 0.07, eps=0.3)
+    _check_elementwise(U, ref, _tol(max(counts), _kappa(nx, ny, nz, 0.05, 0.06, 0.07)), f"{dims}")
+
+
+def test_closed_form_has_no_line_bound():
+    """The same bound does not refuse a grid in closed form (no line solves)."""
+    print("[case] closed 3275 x 1023 x 1", flush=True)
+    _tdt().Poisson3D(3275, 1023, 1, 0.05, 0.06, 0.07, 0.3)
