@@ -866,6 +866,9 @@ tdt_status_t mark_short(tdt_plan_s* p, int dir) {
   std::vector<char>& ok = p->short_ok[dir];
   ok.assign(S, 0);
   if (p->B != tdt::kShortB) return TDT_OK;
+  // the interface pass solves a float plan's corner rows in double, and the
+  // double gradients of psi and chi are sums over them alone
+  if (p->quasi && p->dtype == TDT_F32) return TDT_OK;
   size_t count = 0;
   for (size_t s = 0; s < S; ++s) {
     ok[s] = p->hsys[dir][s].ntiles == 1 &&
@@ -1398,7 +1401,10 @@ int64_t series_fslots(const tdt_plan_s* p, int64_t M) {
 // The narrowest workgroup that keeps at least 85 % as many lanes at work as
 // the best width does: narrow workgroups wait for fewer wavefronts and need
 // no LDS level (64 lanes), wider ones waste fewer lanes on system sizes that
-// do not divide them.
+// do not divide them.  A float plan's systems share a workgroup only where
+// none straddles a row of 16 lanes or a wavefront: every sum is then formed in
+// the tile kernels' order and X is theirs bit for bit (single floats of X
+// moved the double gradients of 5000 systems of 100 rows by 2e-9 otherwise).
 void short_runs(const tdt_plan_s* p, int dir, int64_t M, int& nt, int& g, int64_t& runs) {
   nt = g = 0;
   runs = 0;
@@ -1406,8 +1412,10 @@ void short_runs(const tdt_plan_s* p, int dir, int64_t M, int& nt, int& g, int64_
   const int nb = (int)((p->hsys[dir][0].n + tdt::kShortB - 1) / tdt::kShortB);
   // systems a workgroup of w lanes holds: its lanes' blocks, and its rows
   // (a quasi-Toeplitz system's two corner rows lie outside its blocks)
+  const bool alone = p->dtype == TDT_F32 && (nb <= 64 ? 64 % nb != 0 : nb % 64 != 0);
   auto fits = [&](int w) {
-    return (int)std::min<int64_t>(w / nb, (int64_t)w * tdt::kShortB / p->N);
+    const int64_t most = std::min<int64_t>(w / nb, (int64_t)w * tdt::kShortB / p->N);
+    return (int)(alone ? std::min<int64_t>(most, 1) : most);
   };
   auto used = [&](int w) { return (double)(fits(w) * nb) / w; };
   double best = 0.0;
@@ -1522,8 +1530,12 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     const SysDesc& D0 = p->hsys[0][0];
     const int64_t nt = D0.ntiles;
     const bool need = needs_interface(D0);
+    // A float series of few tiles with a ragged last one keeps that tile's
+    // float sweep: the supports' double sums move single floats of X next to
+    // its edge, and with few rows the double gradients' sums by up to 1e-9.
+    const bool sweep = p->dtype == TDT_F32 && D0.n % p->L != 0 && nt < 4;
     const bool itf =
-        need && !(p->hsys[dir][0].halo &&
+        need && !(p->hsys[dir][0].halo && !sweep &&
                   halo_pays(p->dtype, p->green_kf[dir] + p->green_kl[dir], M * nt));
     L.halo = need && !itf ? 1 : 0;
     L.p1_items = nullptr;

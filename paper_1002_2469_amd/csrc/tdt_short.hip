@@ -625,9 +625,12 @@ hipError_t run_short(const LaunchSet& L, const void* F, void* X, const void* Xfw
   A.iters = L.iters;
   A.max_iter = L.max_iter;
   A.refine_tol = L.refine_tol;
-  if (L.quasi)
-    return bwd ? by_width<Tio, Tc, REFINE, true, true>(nt, L, A, st)
-               : by_width<Tio, Tc, REFINE, false, true>(nt, L, A, st);
+  if constexpr (sizeof(Tio) == 8) {
+    if (L.quasi)
+      return bwd ? by_width<Tio, Tc, REFINE, true, true>(nt, L, A, st)
+                 : by_width<Tio, Tc, REFINE, false, true>(nt, L, A, st);
+  }
+  if (L.quasi) return hipErrorInvalidValue;   // (float plans: mark_short)
   return bwd ? by_width<Tio, Tc, REFINE, true, false>(nt, L, A, st)
              : by_width<Tio, Tc, REFINE, false, false>(nt, L, A, st);
 }
