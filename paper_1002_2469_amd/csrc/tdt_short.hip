@@ -11,7 +11,8 @@
 // from the left and its last nothing from the right, so a value of another
 // system never enters, whatever it is), and the correction.  The corner rows
 // of a quasi-Toeplitz system (eq. (21)) are the one-row segments at the two
-// ends of its own chain of blocks: no first pass and no interface launch.
+// ends of its own chain of blocks: no first pass and no interface launch
+// (double and refined plans).
 //
 // The rows of the workgroup's systems are one contiguous run, loaded and
 // stored coalesced; LDS holds the run with 16 bytes of padding after every
