@@ -83,7 +83,6 @@ struct tdt_plan_s {
   std::vector<char> short_ok[2];
   int qnt = 0;
   double* dqtab64[2] = {nullptr, nullptr};
-  float* dqtab32[2] = {nullptr, nullptr};
   double* dgreen[2] = {nullptr, nullptr};   // series with several tiles: [2][L]
   // rows of a tile the first pass reads from the head and the tail (0: all)
   int green_kf[2] = {0, 0}, green_kl[2] = {0, 0};
@@ -652,7 +651,6 @@ void destroy(tdt_plan_s* p) {
     (void)hipFree(p->dtab64[k]);
     (void)hipFree(p->dtab32[k]);
     (void)hipFree(p->dqtab64[k]);
-    (void)hipFree(p->dqtab32[k]);
     (void)hipFree(p->dgreen[k]);
     (void)hipFree(p->dttab[k]);
     (void)hipFree(p->dgrow[k]);
@@ -825,9 +823,9 @@ tdt_status_t build_varlen_lists(tdt_plan_s* p) {
 // path: beta_{m-1} and 1/(1 - phi_first beta_{m-1}) of its blocks with the
 // elimination started from the first corner row (beta_{-1} = -t_1/(t_0+psi),
 // where the tiles' table starts from 0), then the closing pivot of the last
-// corner row and the two corner diagonal entries.  False if a pivot vanishes
-// (the system then goes through the interface pass).
-bool corner_table(const SysDesc& D, double psi, double chi, int NT, double* t64, float* t32) {
+// corner row.  False if a pivot vanishes (the system then goes through the
+// interface pass).
+bool corner_table(const SysDesc& D, int NT, double* t64) {
   const int nb = (int)((D.n + tdt::kShortB - 1) / tdt::kShortB);
   ld tail[4] = {D.blk[0], D.blk[1], D.blk[2], D.blk[3]};
   const int bt = (int)((D.n - 1) % tdt::kShortB) + 1;
@@ -846,11 +844,7 @@ bool corner_table(const SysDesc& D, double psi, double chi, int NT, double* t64,
   }
   const ld den = 1.0L - (ld)D.qc[3] * beta;
   if (!(std::fabs((double)den) > 1e-13)) return false;
-  double* q = t64 + 2 * NT;
-  q[tdt::kQTabClose] = (double)(1.0L / den);
-  q[tdt::kQTabD0] = (double)((ld)D.b + psi);
-  q[tdt::kQTabD1] = (double)((ld)D.b + chi);
-  for (int k = 0; k < 2 * NT + tdt::kQTabN; ++k) t32[k] = (float)t64[k];
+  t64[tdt::kTabN * NT + tdt::kQTabClose] = (double)(1.0L / den);
   return true;
 }
 
@@ -883,14 +877,10 @@ tdt_status_t mark_short(tdt_plan_s* p, int dir) {
   p->qnt = p->varlen ? tdt::kShortItemNT : p->NT;
   const size_t pitch = (size_t)tdt::kTabN * p->qnt + tdt::kQTabN;
   std::vector<double> q64(S * pitch, 0.0);
-  std::vector<float> q32(S * pitch, 0.0f);
   for (size_t s = 0; s < S; ++s)
     if (ok[s])
-      ok[s] = corner_table(p->hsys[dir][s], p->in_psi[s], p->in_chi[s], p->qnt,
-                           q64.data() + s * pitch, q32.data() + s * pitch);
-  tdt_status_t st = dev_upload(&p->dqtab64[dir], q64.data(), q64.size());
-  if (st == TDT_OK) st = dev_upload(&p->dqtab32[dir], q32.data(), q32.size());
-  return st;
+      ok[s] = corner_table(p->hsys[dir][s], p->qnt, q64.data() + s * pitch);
+  return dev_upload(&p->dqtab64[dir], q64.data(), q64.size());
 }
 
 // Build both descriptor sets (T and T^T) and upload everything.  sizes and
@@ -1465,7 +1455,6 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
   L.gen_tK = p->dgtK[dir];
   L.gen_M = M;
   L.qtab64 = p->dqtab64[dir];
-  L.qtab32 = p->dqtab32[dir];
   L.qnt = p->qnt;
   if (p->general) {
     const SysDesc& D0 = p->hsys[0][0];

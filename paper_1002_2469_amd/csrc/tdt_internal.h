@@ -116,11 +116,10 @@ enum { kGenPF = 0, kGenPL = 1, kGenCF = 2, kGenBP = 3, kGenID = 4, kGenBlkN = 5 
 // varlen plan gives each such system (up to kShortItemNT blocks) a workgroup
 // of kShortItemNT lanes of its own.  Quasi-Toeplitz plans hold a second
 // per-position table for them, whose elimination starts from the first
-// corner row; after its positions: 1/(1 - qc[3] beta_last) and the two corner
-// diagonal entries.
+// corner row; after its positions: 1/(1 - qc[3] beta_last).
 constexpr int kShortB = 16;
 constexpr int kShortItemNT = 64;
-enum { kQTabClose = 0, kQTabD0 = 1, kQTabD1 = 2, kQTabN = 4 };
+enum { kQTabClose = 0, kQTabN = 2 };
 
 // Everything one solve launch sequence needs (device pointers).
 struct LaunchSet {
@@ -166,7 +165,6 @@ struct LaunchSet {
   const int* short_items;
   int64_t n_short;
   const double* qtab64;   // quasi-Toeplitz: [ncidx][2 qnt + kQTabN]
-  const float* qtab32;
   int qnt;
   int halo;               // the final pass forms its tiles' outside values (SysDesc halo)
   int64_t corner0;        // series, quasi-Toeplitz: first corner t-gradient slot

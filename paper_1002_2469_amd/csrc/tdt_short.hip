@@ -12,7 +12,8 @@
 // system never enters, whatever it is), and the correction.  The corner rows
 // of a quasi-Toeplitz system (eq. (21)) are the one-row segments at the two
 // ends of its own chain of blocks: no first pass and no interface launch
-// (double and refined plans).
+// (double and refined plans; in refined ones that chain runs in double before
+// the float solves, as the interface pass does for tiles).
 //
 // The rows of the workgroup's systems are one contiguous run, loaded and
 // stored coalesced; LDS holds the run with 16 bytes of padding after every
@@ -36,12 +37,14 @@ struct ShortArgs {
   const SysDesc* __restrict__ sys;
   const double* __restrict__ vec64;
   const float* __restrict__ vec32;
-  const double* __restrict__ tab64;   // [ncidx][tabld]: beta_{m-1}, then 1/(1 - phi_f beta_{m-1})
-  const float* __restrict__ tab32;    //   of tabnt positions each; quasi-Toeplitz: kQTabN more
+  const double* __restrict__ tab64;   // [ncidx][kTabN tabnt]: beta_{m-1}, then
+  const float* __restrict__ tab32;    //   1/(1 - phi_f beta_{m-1}) of tabnt positions each
+  const double* __restrict__ qtab64;  // quasi-Toeplitz: [ncidx][2 qnt + kQTabN], the chain with
+                                      //   its corner rows
   const int* __restrict__ items;      // varlen: one system per workgroup; null for a series
   int64_t nitems;                     // workgroups' worth of systems
   int64_t M;                          // series: right-hand sides
-  int tabnt, tabld;
+  int tabnt, qnt;
   int G;                              // systems per workgroup
   double* __restrict__ gpart;
   int* __restrict__ iters;
@@ -155,12 +158,17 @@ __device__ __forceinline__ void cut_scan_bwd(const Block<Tc>& b, Tc& C, Tc& h, T
 }
 
 // Solves the workgroup's systems for the right-hand side rows in q (0 past
-// len); fl, fr: the corner rows' right-hand sides (quasi-Toeplitz, in the
-// first and last lane of a system), out: the corner unknowns there.
-template <int NW, typename Tc, bool QUASI>
+// len).  What lies outside a system, in its first and last lane:
+//   kOpen   nothing
+//   kGiven  the values fl and fr
+//   kChain  its corner rows (quasi-Toeplitz), fl and fr their right-hand
+//           sides; out: the corner unknowns.  kEnds: these alone, q not solved.
+enum { kOpen, kGiven, kChain, kEnds };
+template <int NW, typename Tc, int OUT>
 __device__ __forceinline__ void short_solve(Tc (&q)[kB], const Block<Tc>& b,
                                             const Consts<Tc>& K, const SysDesc& S, Tc qs5,
                                             Tc& fl, Tc& fr, Tc (*fw)[2], Tc (*bw)[2]) {
+  constexpr bool CHAIN = OUT == kChain || OUT == kEnds;
   const int lane = threadIdx.x & 63;
   const bool wave_tail = __ballot(b.len > 0 && b.len < kB) != 0;
   const cptr<Tc> iu = fresh(K.iu), aiu = fresh(K.aiu);
@@ -181,39 +189,42 @@ __device__ __forceinline__ void short_solve(Tc (&q)[kB], const Block<Tc>& b,
   for (int i = kB - 2; i >= 0; --i) q[i] -= cpb[i] * q[i + 1];
   const Tc yf = q[0];
   Tc yl = q[kB - 1];
-  if (QUASI && wave_tail) {
+  if (CHAIN && wave_tail) {
 #pragma unroll
     for (int i = 0; i + 1 < kB; ++i)
       if (i == b.len - 1) yl = q[i];
   }
   // the interface recurrences (see tile_solve), each system's own
-  const Tc alpha_in = QUASI && b.first ? fl * (Tc)S.qc[0] : Tc(0);
+  const Tc alpha_in = OUT != kOpen && b.first ? (CHAIN ? fl * (Tc)S.qc[0] : fl) : Tc(0);
   const Tc A0 = b.pl * b.iD;
   Tc A = A0;
   Tc g = yl + A0 * b.bp * yf;
-  if (QUASI && b.first) g += A0 * alpha_in;
+  if (OUT != kOpen && b.first) g += A0 * alpha_in;
   Tc cin, ein;
   cut_scan_fwd<NW>(b, A, g, fw, cin);
   const Tc alpha = A * cin + g;
   Tc alpha_prev = __shfl_up(alpha, 1, 64);
   if (lane == 0) alpha_prev = cin;
   if (b.first) alpha_prev = alpha_in;
-  // the unknown right of the system: its last corner row, or nothing
-  const Tc u_right = QUASI && b.last ? (fr * (Tc)S.qc[2] + (Tc)S.qc[3] * alpha) * qs5 : Tc(0);
+  // the unknown right of the system: its last corner row, a value, or nothing
+  const Tc u_right = OUT != kOpen && b.last
+                         ? (CHAIN ? (fr * (Tc)S.qc[2] + (Tc)S.qc[3] * alpha) * qs5 : fr)
+                         : Tc(0);
   const Tc C0 = b.cf * b.iD;
   Tc C = C0;
   Tc h = (yf + b.pf * alpha_prev) * b.iD;
-  if (QUASI && b.last) h += C0 * u_right;
+  if (OUT != kOpen && b.last) h += C0 * u_right;
   cut_scan_bwd<NW>(b, C, h, bw, ein);
   const Tc u = C * ein + h;
   Tc u_next = __shfl_down(u, 1, 64);
   if (lane == 63) u_next = ein;
   const Tc xl = alpha_prev + b.bp * u;            // last unknown of the previous block
   const Tc xr = b.last ? u_right : u_next;        // first unknown of the next block
-  if (QUASI) {
+  if (CHAIN) {
     fl = xl;
     fr = xr;
   }
+  if constexpr (OUT == kEnds) return;
   if (b.len == kB) {
     const cptr<Tc> phi = fresh(K.phi), chi = fresh(K.chi);
 #pragma unroll
@@ -226,7 +237,7 @@ __device__ __forceinline__ void short_solve(Tc (&q)[kB], const Block<Tc>& b,
     for (int i = 0; i < kB; ++i) {
       const Tc ynext = i + 1 < kB ? q[i + 1] : Tc(0);
       Tc dp = q[i] + K.cp[i] * ynext + delta;
-      if (QUASI && i == b.len - 1) dp -= K.cp[i] * xr;
+      if (OUT != kOpen && i == b.len - 1) dp -= K.cp[i] * xr;
       q[i] = i < b.len ? dp : Tc(0);
       if (i + 1 < kB) delta = -K.aiu[i + 1] * delta;
     }
@@ -264,6 +275,8 @@ __global__ __launch_bounds__(NT, kMinWavesPerSimd) void k_short(ShortArgs<Tio> A
   __shared__ double red[NW][kGradN];
   __shared__ int smax[REFINE ? NT : 1];
   __shared__ double edge[REFINE ? NW : 1][2];
+  // refined quasi-Toeplitz systems: the double chain's exchange
+  __shared__ double fwd[REFINE && QUASI ? NW : 1][2], bwd[REFINE && QUASI ? NW : 1][2];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   int it_max = 0;
   float est_max = 0.0f;
@@ -291,21 +304,22 @@ __global__ __launch_bounds__(NT, kMinWavesPerSimd) void k_short(ShortArgs<Tio> A
     b.last = b.rb == 0;
     b.len = live ? (n - b.blk * kB < kB ? n - b.blk * kB : kB) : 0;
     const Consts<Tc> K = make_consts<SH, Tc>(S, A.vec64, A.vec32);
-    Tc qs5 = Tc(0);
-    double d0 = 0.0, d1 = 0.0;   // t_0 + psi, t_0 + chi
-    {
+    const double* qt = nullptr;
+    double qs5 = 0.0;
+    if constexpr (QUASI) {
+      qt = A.qtab64 + (int64_t)S.cidx * (kTabN * A.qnt + kQTabN);
+      qs5 = as_const(qt)[kTabN * A.qnt + kQTabClose];
+    }
+    if constexpr (QUASI && !REFINE) {
+      b.bp = qt[b.blk];
+      b.iD = qt[A.qnt + b.blk];
+    } else {
       const Tc* tb;
-      if constexpr (sizeof(Tc) == 8) tb = A.tab64 + (int64_t)S.cidx * A.tabld;
-      else tb = A.tab32 + (int64_t)S.cidx * A.tabld;
-      const int ti = !QUASI && S.tfix > 0 && b.blk > S.tfix ? S.tfix : b.blk;
+      if constexpr (sizeof(Tc) == 8) tb = A.tab64 + (int64_t)S.cidx * kTabN * A.tabnt;
+      else tb = A.tab32 + (int64_t)S.cidx * kTabN * A.tabnt;
+      const int ti = S.tfix > 0 && b.blk > S.tfix ? S.tfix : b.blk;
       b.bp = tb[ti];
       b.iD = tb[A.tabnt + ti];
-      if constexpr (QUASI) {
-        qs5 = as_const(tb)[2 * A.tabnt + kQTabClose];
-        const cptr<double> td = as_const(A.tab64 + (int64_t)S.cidx * A.tabld + 2 * A.tabnt);
-        d0 = td[kQTabD0];
-        d1 = td[kQTabD1];
-      }
     }
     b.pf = K.pf;
     b.pl = K.pl;
@@ -332,6 +346,7 @@ __global__ __launch_bounds__(NT, kMinWavesPerSimd) void k_short(ShortArgs<Tio> A
     auto flat = [&](int e) -> Tio& { return lds[e + (e / kB) * PAD]; };
     const int ecl = live ? sl * N : 0, ecr = live ? sl * N + N - 1 : 0;   // corner rows
     Tc fl = Tc(0), fr = Tc(0);
+    constexpr int OUT = !QUASI ? kOpen : (REFINE ? kGiven : kChain);
     if constexpr (!REFINE) {
       Tc q[kB];
 #pragma unroll
@@ -343,16 +358,50 @@ __global__ __launch_bounds__(NT, kMinWavesPerSimd) void k_short(ShortArgs<Tio> A
         if (b.first) fl = (Tc)flat(ecl);
         if (b.last) fr = (Tc)flat(ecr);
       }
-      short_solve<NW, Tc, QUASI>(q, b, K, S, qs5, fl, fr, fw, bw);
+      short_solve<NW, Tc, OUT>(q, b, K, S, (Tc)qs5, fl, fr, fw, bw);
 #pragma unroll
       for (int i = 0; i < kB; ++i)
         if (i < b.len) at(i) = (Tio)q[i];
     } else {
       // iterative refinement as in the tile kernels, each system by its own
-      // stopping test (a system that has met it keeps its iterate)
+      // stopping test (a system that has met it keeps its iterate); the corner
+      // unknowns come from the double chain first and stay.  (Refined with the
+      // inner rows instead, by one float chain, they were off by 2e-15 to
+      // 2e-14 of the largest unknown where the double chain leaves 1e-16; 65793
+      // systems of 255 rows 82 and 88 us, the adjoint 168 and 166.)
       const double a = S.a, bb = S.b, c = S.c;
       double x[kB], xcl = 0.0, xcr = 0.0;
       float vloc = 0.0f;
+      if constexpr (QUASI) {
+        const Consts<double> K64 = make_consts<SH, double>(S, A.vec64, A.vec32);
+        Block<double> d;
+        d.blk = b.blk;
+        d.rb = b.rb;
+        d.len = b.len;
+        d.first = b.first;
+        d.last = b.last;
+        d.bp = qt[b.blk];
+        d.iD = qt[A.qnt + b.blk];
+        d.pf = K64.pf;
+        d.pl = K64.pl;
+        d.cf = K64.cf;
+        if (b.last && n % kB != 0) {
+          d.pf = K64.tail_pf;
+          d.pl = K64.tail_pl;
+          d.cf = K64.tail_cf;
+        }
+        double q[kB];
+#pragma unroll
+        for (int i = 0; i < kB; ++i) {
+          const double f = (double)at(i);
+          q[i] = i < b.len ? f : 0.0;
+        }
+        if (b.first) xcl = (double)flat(ecl);
+        if (b.last) xcr = (double)flat(ecr);
+        short_solve<NW, double, kEnds>(q, d, K64, S, qs5, xcl, xcr, fwd, bwd);
+        fl = (Tc)xcl;
+        fr = (Tc)xcr;
+      }
       {
         Tc q[kB];
 #pragma unroll
@@ -360,24 +409,13 @@ __global__ __launch_bounds__(NT, kMinWavesPerSimd) void k_short(ShortArgs<Tio> A
           const Tc f = (Tc)at(i);
           q[i] = i < b.len ? f : Tc(0);
         }
-        if (QUASI) {
-          if (b.first) fl = (Tc)flat(ecl);
-          if (b.last) fr = (Tc)flat(ecr);
-        }
-        short_solve<NW, Tc, QUASI>(q, b, K, S, qs5, fl, fr, fw, bw);
+        short_solve<NW, Tc, OUT>(q, b, K, S, Tc(0), fl, fr, fw, bw);
 #pragma unroll
         for (int i = 0; i < kB; ++i) {
           x[i] = (double)q[i];
           vloc = fmaxf(vloc, fabsf((float)q[i]));
         }
-        if (QUASI && live && b.first) {
-          xcl = (double)fl;
-          vloc = fmaxf(vloc, fabsf((float)fl));
-        }
-        if (QUASI && live && b.last) {
-          xcr = (double)fr;
-          vloc = fmaxf(vloc, fabsf((float)fr));
-        }
+        fl = fr = Tc(0);   // the corrections have nothing outside
       }
       const float xmax = system_max(vloc, sl, smax);
       float dprev = xmax, est = 1.0f;   // est: remaining relative error (1: no update ran)
@@ -406,31 +444,13 @@ __global__ __launch_bounds__(NT, kMinWavesPerSimd) void k_short(ShortArgs<Tio> A
           r = fma(-c, right, r);
           q[i] = i < b.len ? (Tc)r : Tc(0);
         }
-        if (QUASI) {
-          if (b.first) fl = (Tc)fma(-c, x[0], fma(-d0, xcl, (double)flat(ecl)));
-          if (b.last) {
-            double xe = x[kB - 1];
-#pragma unroll
-            for (int i = 0; i + 1 < kB; ++i)
-              if (i == b.len - 1) xe = x[i];
-            fr = (Tc)fma(-a, xe, fma(-d1, xcr, (double)flat(ecr)));
-          }
-        }
-        short_solve<NW, Tc, QUASI>(q, b, K, S, qs5, fl, fr, fw, bw);
+        short_solve<NW, Tc, OUT>(q, b, K, S, Tc(0), fl, fr, fw, bw);
         vloc = 0.0f;
         if (!done) {
 #pragma unroll
           for (int i = 0; i < kB; ++i) {
             x[i] += (double)q[i];
             vloc = fmaxf(vloc, fabsf((float)q[i]));
-          }
-          if (QUASI && b.first) {
-            xcl += (double)fl;
-            vloc = fmaxf(vloc, fabsf((float)fl));
-          }
-          if (QUASI && b.last) {
-            xcr += (double)fr;
-            vloc = fmaxf(vloc, fabsf((float)fr));
           }
         }
         ++it;
@@ -614,10 +634,11 @@ hipError_t run_short(const LaunchSet& L, const void* F, void* X, const void* Xfw
   A.sys = L.sys;
   A.vec64 = L.vec64;
   A.vec32 = L.vec32;
-  A.tabnt = L.quasi ? L.qnt : kShapes[L.shape].NT;
-  A.tabld = kTabN * A.tabnt + (L.quasi ? kQTabN : 0);
-  A.tab64 = L.quasi ? L.qtab64 : L.tab64;
-  A.tab32 = L.quasi ? L.qtab32 : L.tab32;
+  A.tabnt = kShapes[L.shape].NT;
+  A.tab64 = L.tab64;
+  A.tab32 = L.tab32;
+  A.qtab64 = L.qtab64;
+  A.qnt = L.qnt;
   A.items = L.n_short > 0 ? L.short_items : nullptr;
   A.nitems = L.n_short > 0 ? L.n_short : L.short_runs;
   A.M = L.short_M;
