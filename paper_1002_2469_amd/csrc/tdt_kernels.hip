@@ -692,7 +692,7 @@ __device__ __forceinline__ void load_tile_item(const TileArgs<Tio>& A, int64_t i
       const int64_t cs0 = A.items ? (int64_t)S.fslot0 + S.ntiles : A.corner0 + 2 * G.I.m;
       if (tid == 0 && G.I.t == 0)
         store_corner<Tio>(A.X, A.Xfwd, A.gpart + kGradN * cs0, sbase, S.n, 0, P.XL);
-      if (tid == kNT - 64 && G.I.t == S.ntiles - 1)
+      if (tid == (HALO ? kNT - 64 : 0) && G.I.t == S.ntiles - 1)
         store_corner<Tio>(A.X, A.Xfwd, A.gpart + kGradN * (cs0 + 1), sbase, S.n, 1, P.XR);
     }
   } else if (!SUMMARY) {
@@ -1192,10 +1192,10 @@ __global__ __launch_bounds__(SH::NT, REFINE ? kRefineWaves : SH::WAVES) void k_t
     }
     const int64_t kn = k + gridDim.x;
     const bool fold = QUASI && !SUMMARY && tl < kTile;
-    if (fold && tid == kNT - 64) sh.xr = XRt;
+    if (HALO && fold && tid == kNT - 64) sh.xr = XRt;
     __syncthreads();
     if (fold) {
-      fold_right<SH>(sh, tl, S.c, sh.xr);
+      fold_right<SH>(sh, tl, S.c, HALO ? sh.xr : XRt);
       __syncthreads();
     }
 
