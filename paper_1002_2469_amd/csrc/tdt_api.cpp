@@ -1391,7 +1391,22 @@ int64_t series_fslots(const tdt_plan_s* p, int64_t M) {
 // The narrowest workgroup that keeps at least 85 % as many lanes at work as
 // the best width does: narrow workgroups wait for fewer wavefronts and need
 // no LDS level (64 lanes), wider ones waste fewer lanes on system sizes that
-// do not divide them.  A float plan's systems share a workgroup only where
+// do not divide them; the narrowest that holds a system while the device
+// holds all of them at once (21 systems of 1500 rows, forward and adjoint
+// kernels: two per 512 lanes 8.8 and 14.4 us, one per 128 6.4 and 10.3).
+//   Refined plans: a pass of these kernels takes about 1.4 times (quasi-
+// Toeplitz ends 1.1) as long as one of the tile kernel, and twice per lane
+// once the device is full, so they are left to that kernel unless half of the
+// lanes are saved and either its workgroups would fill three quarters of the
+// device (half, against single wavefronts) or the workgroups here are an
+// eighth (quasi-Toeplitz: a half) as wide.  us forward,
+// tile kernel and short (shape 16 x 512; 8388608 rows and few systems):
+//   2100 rows: 3994 systems 95 and 66, 15 systems 12.2 and 18.4;
+//   700 rows: 11983 systems 262 and 51, 46 systems 12.2 and 14.8;
+//   300 rows: 109 systems 12.2 and 12.0;
+//   quasi-Toeplitz, 4500 rows (as wide): 1864 systems 78 and 105; 4096 rows
+//   (half as wide): 2048 systems 77 and 54, 8 systems 20.2 and 17.8.
+// A float plan's systems share a workgroup only where
 // none straddles a row of 16 lanes or a wavefront: every sum is then formed in
 // the tile kernels' order and X is theirs bit for bit (single floats of X
 // moved the double gradients of 5000 systems of 100 rows by 2e-9 otherwise).
@@ -1408,21 +1423,28 @@ void short_runs(const tdt_plan_s* p, int dir, int64_t M, int& nt, int& g, int64_
     return (int)(alone ? std::min<int64_t>(most, 1) : most);
   };
   auto used = [&](int w) { return (double)(fits(w) * nb) / w; };
+  // lanes the device holds at once at these kernels' registers
+  const int64_t lanes = (int64_t)tdt::device_cus() * 1024;
   double best = 0.0;
   for (int w = 64; w <= p->NT; w *= 2) best = std::max(best, used(w));
   for (int w = 64; w <= p->NT && best > 0.0; w *= 2)
-    if (used(w) >= 0.85 * best) {
+    if (used(w) >= 0.85 * best || (fits(w) > 0 && M * w <= lanes)) {
       nt = w;
       break;
     }
   if (nt == 0) return;
   g = fits(nt);
-  // a whole workgroup of the plan's shape per system: the tile kernels do that
-  if (g == 1 && nt == p->NT && !p->quasi) {
-    nt = g = 0;
-    return;
-  }
   runs = (M + g - 1) / g;
+  // a whole workgroup of the plan's shape per system: the tile kernels do that
+  bool pays = g > 1 || nt < p->NT || (p->quasi && p->dtype != TDT_F32_REFINE);
+  if (p->dtype == TDT_F32_REFINE) {
+    const bool full = 4 * M * p->NT > (nt == 64 ? 2 : 3) * lanes;
+    pays = 2 * runs * nt <= M * p->NT && (full || p->NT >= (p->quasi ? 2 : 8) * nt);
+  }
+  if (!pays) {
+    nt = g = 0;
+    runs = 0;
+  }
 }
 
 // The launch set of a solve (everything but the workspace and the profile
