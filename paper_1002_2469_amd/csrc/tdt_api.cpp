@@ -688,9 +688,21 @@ void destroy(tdt_plan_s* p) {
 //               192 + 192: 216/202  227/208  114/127  384 + 384: 220/225 226/237 117/150
 //   300 x 30011 256 + 256: 42/36  51/42  27/26       576 + 576: 43/39  53/47  28/34
 //   65536 rows  576 + 576: 11.6/9.1  14.1/11.8  11.3/8.9
-bool halo_pays(tdt_dtype_t dtype, int64_t rows, int64_t tiles) {
-  if (dtype == TDT_F32)
-    return rows <= 256 || (rows <= 512 && tiles <= 2048) || tiles <= 256;
+// Float with more than 256 rows, so, while the tiles are about one round of
+// resident workgroups (256 + 256, systems of 65536 rows: 512 tiles of 512
+// lanes 13.3/11.2, 600 14.7/16.7, 2048 31/39; of 256 lanes 1088 13.6/11.6,
+// 1296 14.3/16.2), three where a ragged last tile would be swept in a launch
+// of its own (30011 rows: 1496 tiles of 512 lanes 24.5/22.5, 1900 33.9/37.3).
+// Refined quasi-Toeplitz systems in blocks of 8 rows, whose kernel is short of
+// registers, forward: 2048 tiles 48/45, 4096 77/85 (64 + 64 to 192 + 192).
+bool halo_pays(const tdt_plan_s* p, int dir, int64_t rows, int64_t tiles, bool ragged) {
+  if (p->dtype == TDT_F32) {
+    const int64_t round = (int64_t)tdt::device_cus() * 1024 / p->NT;
+    return rows <= 256 || tiles <= 256 ||
+           (rows <= 512 && tiles <= std::min<int64_t>(ragged ? 3 * round : round + round / 16, 2048));
+  }
+  if (p->dtype == TDT_F32_REFINE && p->quasi && p->B == 8 && dir == 0 && tiles > 2048)
+    return false;
   return rows <= 512 || tiles <= 2048;
 }
 
@@ -971,16 +983,17 @@ tdt_status_t finish_plan(tdt_plan_s* p, const std::vector<double>& tm1,
       // launch is there anyway, and the others do better in it:
       // separation-of-variables batch 94.5 us, 98 with them in the final pass
       // alone; 1000 quasi-Toeplitz systems with refinement 149 and 182.
-      bool all = true;
+      bool all = true, ragged = false;
       int64_t rows = 0, tiles = 0;
       for (int64_t s = 0; s < S; ++s) {
         const SysDesc& D = p->hsys[dir][s];
         if (p->short_ok[dir][s]) continue;
         tiles += D.ntiles;
+        ragged = ragged || D.n % kTile != 0;
         rows = std::max<int64_t>(rows, D.gkf + D.gkl);
         if (needs_interface(D) && !D.halo) all = false;
       }
-      if (!all || !halo_pays(p->dtype, rows, tiles))
+      if (!all || !halo_pays(p, dir, rows, tiles, ragged))
         for (SysDesc& D : p->hsys[dir]) D.halo = 0;
       (void)hipFree(p->dgpack[dir]);
       p->dgpack[dir] = nullptr;
@@ -1547,7 +1560,8 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     const bool sweep = p->dtype == TDT_F32 && D0.n % p->L != 0 && nt < 4;
     const bool itf =
         need && !(p->hsys[dir][0].halo && !sweep &&
-                  halo_pays(p->dtype, p->green_kf[dir] + p->green_kl[dir], M * nt));
+                  halo_pays(p, dir, p->green_kf[dir] + p->green_kl[dir], M * nt,
+                            D0.n % p->L != 0));
     L.halo = need && !itf ? 1 : 0;
     L.p1_items = nullptr;
     L.fin_items = nullptr;
