@@ -224,13 +224,16 @@ tdt_status_t tdt_poisson2d_create(int64_t nx, int64_t ny, double hx, double hy,
  * solves that may run concurrently (shared workspace). */
 tdt_status_t tdt_poisson2d_solve(tdt_poisson_t p, const double *F, double *U,
                                  hipStream_t stream);
-/* The handle's line plan (owned by the handle), e.g. to set its options or
- * autotune it: a varlen plan, or the strided plan of the in-place path
- * (which takes no options).  Where Nx+1 is not a power of two, asking for it
- * moves an in-place handle to mode-major order and a varlen plan, for this
- * and every later solve (blocking; TDT_ERR_OOM and the handle unchanged if
- * its buffers cannot be had): not while a solve may run or is being
- * captured. */
+/* The handle's line plan (owned by the handle), e.g. to set its options,
+ * autotune it or read its profile: a varlen plan, or the strided plan of the
+ * in-place path where Nx+1 is a power of two (which takes no options).  An
+ * in-place handle of another Nx builds a varlen plan and 2 Nx Ny doubles of
+ * workspace when first asked (blocking, not while a stream is being captured;
+ * TDT_ERR_OOM and the handle unchanged if they cannot be had).  Its solves
+ * stay in place, recorded in that plan's profile, as long as the plan's
+ * launch options (TDT_OPT_WHOLE_MAX_TILES, _WG_PER_CU, _SHAPE) have their
+ * defaults, and go through it in mode-major order while they have not.
+ * Solves captured before stay valid until the handle is destroyed. */
 tdt_status_t tdt_poisson2d_line_plan(tdt_poisson_t p, tdt_plan_t *line);
 /* HIP events around the forward transform (with the transpose to mode-major
  * order on that path), the line solve and the inverse transform of every

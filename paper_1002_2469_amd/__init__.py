@@ -467,7 +467,10 @@ class Poisson2D:
         return dict(first_pass_ms=ms[0], interface_ms=ms[1], final_ms=ms[2], solves=n.value)
 
     def set_line_option(self, name: str, value: int):
-        """A launch option of the line plan (see Plan.set_option)."""
+        """A launch option of the line plan (see Plan.set_option).  Where the
+        modes are solved in place, they go through that plan in mode-major
+        order while an option differs from its default (not possible where
+        nx + 1 is a power of two)."""
         _lib.check(_lib.lib().tdt_plan_set_option(self._line(), _lib.OPTIONS[name], int(value)),
                    "tdt_plan_set_option")
 

@@ -122,6 +122,7 @@ struct tdt_plan_s {
   // measurement
   bool profile = false;
   std::vector<hipEvent_t> prof_ev;   // 4 per recorded solve
+  tdt_plan_s* prof_to = nullptr;     // strided: the plan whose record the solves go to
 };
 
 // ---------------------------------------------------------------------------
@@ -1744,6 +1745,12 @@ int strided_tiled_tables(int64_t N, int64_t P, const double* tm1, const double* 
   }
   return TDT_OK;
 }
+void strided_profile_to(tdt_plan_s* strided, tdt_plan_s* rec) { strided->prof_to = rec; }
+
+bool launch_options_set(const tdt_plan_s* p) {
+  return p->sys_max_tiles != kSysMaxTilesDefault || p->wg_per_cu != 0 || p->shape != 0;
+}
+
 void strided_sup(int64_t P, const double* tm1, const double* t0, const double* t1, int64_t NL,
                  std::vector<int>& sup, std::vector<double>& geo) {
   const int64_t G = (P + kStrGroup - 1) / kStrGroup;
@@ -2169,14 +2176,15 @@ tdt_status_t tdt_solve_strided(tdt_plan_t p, const double* F, double* X, int64_t
   a.ldb = ldb;
   a.C = p->sC;
   hipEvent_t* ev = nullptr;
-  if (p->profile) {
+  tdt_plan_s* rec = p->prof_to ? p->prof_to : p;
+  if (rec->profile) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
-      const size_t k = p->prof_ev.size();
-      p->prof_ev.resize(k + 4);
+      const size_t k = rec->prof_ev.size();
+      rec->prof_ev.resize(k + 4);
       for (size_t j = 0; j < 4; ++j)
-        if (hipEventCreate(&p->prof_ev[k + j]) != hipSuccess) return TDT_ERR_HIP;
-      ev = p->prof_ev.data() + k;
+        if (hipEventCreate(&rec->prof_ev[k + j]) != hipSuccess) return TDT_ERR_HIP;
+      ev = rec->prof_ev.data() + k;
       for (int j = 0; j < 3; ++j) (void)hipEventRecord(ev[j], stream);
     }
   }

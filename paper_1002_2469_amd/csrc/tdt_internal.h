@@ -192,6 +192,12 @@ struct LaunchSet {
 // its workspace needs, dtype = the plan's.  Returns a tdt_status_t.
 int series_solve_prepare(tdt_plan_s* p, const void* F, void* X, int64_t M, LaunchSet& L,
                          int64_t& slots, int& dtype);
+// A strided plan's solves recorded in another plan's profile, and whether a
+// varlen plan's launch options differ from their defaults (a Poisson handle's
+// line plan).
+void strided_profile_to(tdt_plan_s* strided, tdt_plan_s* rec);
+bool launch_options_set(const tdt_plan_s* p);
+
 // dtype: 0 double, 1 float, 2 float sweeps with double refinement.
 hipError_t launch_solve(int dtype, bool bwd, const LaunchSet& L, const void* F, void* X,
                         const void* Xfwd, hipStream_t st);

@@ -26,6 +26,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <exception>
 #include <new>
 #include <vector>
 
@@ -37,6 +38,7 @@
 struct tdt_poisson_s {
   int64_t nx = 0, ny = 0;
   double hx = 0.0, hy = 0.0;
+  tdt_plan_t opts = nullptr;     // in place: the varlen plan tdt_poisson2d_line_plan hands out
   tdt_plan_t line = nullptr;     // Nx Toeplitz systems of Ny rows (mode-major), or
   bool strided = false;          // the same systems in place in the row-major
   int64_t ldw = 0;               // transformed rows (a strided plan), rows ldw apart
@@ -701,6 +703,7 @@ void destroy_poisson(tdt_poisson_s* p) {
   if (!p) return;
   (void)hipDeviceSynchronize();
   if (p->line) (void)tdt_plan_destroy(p->line);
+  if (p->opts) (void)tdt_plan_destroy(p->opts);
   if (p->fft_made) (void)hipfftDestroy(p->fft);
   for (hipEvent_t e : p->ev) (void)hipEventDestroy(e);
   (void)hipFree(p->sn);
@@ -868,7 +871,9 @@ tdt_status_t tdt_poisson2d_solve(tdt_poisson_t p, const double* F, double* U,
     if (ev) (void)hipEventRecord(ev[j], stream);
   };
   const double s = p->hy * p->hy * 2.0 / (double)(nx + 1);
-  if (p->strided) {
+  // (in place unless launch options were set on the varlen plan handed out)
+  const bool moved = p->opts && tdt::launch_options_set(p->opts);
+  if (p->strided && !moved) {
     // rows' sine transforms (the forward one scaled) into the padded work
     // rows, the mode systems solved in place down the columns, the inverse
     // transforms into U
@@ -892,7 +897,7 @@ tdt_status_t tdt_poisson2d_solve(tdt_poisson_t p, const double* F, double* U,
     hipLaunchKernelGGL(k_transpose_scale, trow, dim3(kTileP, 8), 0, stream, p->y, p->T, ny, nx,
                        s);
     mark(1);
-    tdt_status_t st = tdt_solve_varlen(p->line, p->T, p->V, stream);
+    tdt_status_t st = tdt_solve_varlen(moved ? p->opts : p->line, p->T, p->V, stream);
     if (st < 0) return st;
     mark(2);
     hipLaunchKernelGGL(k_transpose_scale, tcol, dim3(kTileP, 8), 0, stream, p->V, p->y, nx, ny,
@@ -957,18 +962,26 @@ tdt_status_t tdt_poisson2d_profile_read(tdt_poisson_t p, double* ms3, int64_t* n
 
 tdt_status_t tdt_poisson2d_line_plan(tdt_poisson_t p, tdt_plan_t* line) {
   if (!p || !line) return TDT_ERR_INVALID_ARG;
-  if (p->any && p->strided) {
-    // a line plan with options was asked for: the mode systems move to
-    // mode-major order and a varlen plan, for this and every later solve
-    std::vector<int64_t> off;
-    std::vector<double> t0, t1((size_t)p->nx, -1.0);
-    mode_systems(p->nx, p->ny, p->hx, p->hy, off, t0);
+  if (!p->any || !p->strided) {
+    *line = p->line;
+    return TDT_OK;
+  }
+  // A line plan that takes options, next to the strided one: the solves stay
+  // in place, and are recorded in its profile, until options are set on it.
+  // Nothing a captured solve uses is freed before the handle is.
+  if (!p->opts) {
     tdt_plan_t v = nullptr;
     double *T = nullptr, *V = nullptr;
-    tdt_status_t st = tdt_plan_varlen_create(p->nx, off.data(), t1.data(), t0.data(), t1.data(),
-                                             TDT_F64, &v);
-    if (st >= 0) st = tdt_plan_reserve(v, 1);
     const size_t bytes = (size_t)(p->nx * p->ny) * sizeof(double);
+    tdt_status_t st = TDT_ERR_OOM;
+    try {
+      std::vector<int64_t> off;
+      std::vector<double> t0, t1((size_t)p->nx, -1.0);
+      mode_systems(p->nx, p->ny, p->hx, p->hy, off, t0);
+      st = tdt_plan_varlen_create(p->nx, off.data(), t1.data(), t0.data(), t1.data(), TDT_F64, &v);
+    } catch (const std::exception&) {   // host tables
+    }
+    if (st >= 0) st = tdt_plan_reserve(v, 1);
     if (st >= 0 && (hipMalloc(&T, bytes) != hipSuccess || hipMalloc(&V, bytes) != hipSuccess))
       st = TDT_ERR_OOM;
     if (st < 0) {
@@ -977,13 +990,12 @@ tdt_status_t tdt_poisson2d_line_plan(tdt_poisson_t p, tdt_plan_t* line) {
       if (v) (void)tdt_plan_destroy(v);
       return st;
     }
-    (void)tdt_plan_destroy(p->line);   // waits for the device
-    p->line = v;
     p->T = T;
     p->V = V;
-    p->strided = false;
+    p->opts = v;
+    tdt::strided_profile_to(p->line, v);
   }
-  *line = p->line;
+  *line = p->opts;
   return TDT_OK;
 }
 
