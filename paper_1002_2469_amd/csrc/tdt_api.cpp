@@ -2097,9 +2097,11 @@ tdt_status_t tdt_plan_strided_create(int64_t N, int64_t P, const double* h_tm1,
   const int64_t K = g.K;
   const int C = g.C;
   const int64_t n1 = g.n_full, n2 = K > 1 ? g.n_last : 0, n3 = K > 1 ? g.n_ends : 0;
-  std::vector<double> tab;
+  std::vector<double> tab, geo;
+  std::vector<int> sup;
   try {
     tab.resize((size_t)(n1 + n2 + n3));
+    if (K > 1) tdt::strided_sup(P, h_tm1, h_t0, h_t1, g.NL, sup, geo);
   } catch (const std::exception&) {   // P too large for the host tables
     return TDT_ERR_OOM;
   }
@@ -2122,13 +2124,8 @@ tdt_status_t tdt_plan_strided_create(int64_t N, int64_t P, const double* h_tm1,
   p->dominance = dom;
   p->kappa = 0.0;
   tdt_status_t s2 = dev_upload(&p->dstr, tab.data(), tab.size());
-  if (s2 == TDT_OK && K > 1) {
-    std::vector<int> sup;
-    std::vector<double> geo;
-    tdt::strided_sup(P, h_tm1, h_t0, h_t1, g.NL, sup, geo);
-    s2 = dev_upload(&p->dsup, sup.data(), sup.size());
-    if (s2 == TDT_OK) s2 = dev_upload(&p->dgeo, geo.data(), geo.size());
-  }
+  if (s2 == TDT_OK) s2 = dev_upload(&p->dsup, sup.data(), sup.size());
+  if (s2 == TDT_OK) s2 = dev_upload(&p->dgeo, geo.data(), geo.size());
   if (s2 != TDT_OK) {
     destroy(p);
     return s2;
