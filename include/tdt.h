@@ -281,7 +281,8 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p);
  * Nx+1 has a one-kernel transform (rows padded to cache lines; half of that,
  * and two factors per mode and line eigenvalue instead of the per-iteration
  * tables, in closed form), else the FFT plan and (2 Nx + 3) Ny Nz doubles
- * (allocated here, blocking).  Errors: bad sizes, spacings or eps ->
+ * (allocated here, blocking; the latter also where padded rows of an iterated
+ * solve cannot be had and Nx+1 is not a power of two from 128 to 8192).  Errors: bad sizes, spacings or eps ->
  * TDT_ERR_INVALID_ARG; allocation -> TDT_ERR_OOM; FFT plan -> TDT_ERR_HIP. */
 typedef struct tdt_poisson3d_s *tdt_poisson3d_t;
 tdt_status_t tdt_poisson3d_create(int64_t nx, int64_t ny, int64_t nz, double hx, double hy,

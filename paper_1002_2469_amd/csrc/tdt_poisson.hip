@@ -1233,14 +1233,11 @@ hipError_t closed_solve(const tdt_poisson3d_s* p, double* v, hipStream_t st) {
   return tdt::launch_dst_columns(p->dsty, a, st);
 }
 
-}  // namespace
-
-extern "C" {
-
-tdt_status_t tdt_poisson3d_create(int64_t nx, int64_t ny, int64_t nz, double hx, double hy,
-                                  double hz, double eps, tdt_poisson3d_t* out) {
-  if (!out) return TDT_ERR_INVALID_ARG;
-  *out = nullptr;
+// A handle; pad: iterated solves of the transforms of tdt_dst.h, which take
+// padded rows, may be chosen.  *padded: they were.
+tdt_status_t make_poisson3d(int64_t nx, int64_t ny, int64_t nz, double hx, double hy, double hz,
+                            double eps, bool pad, bool* padded, tdt_poisson3d_t* out) {
+  *padded = false;
   const int64_t lmax = tdt::kStrMaxN;
   if (nx < 1 || ny < 1 || nz < 1 || ny > lmax || nz > lmax || nx > (1 << 20) ||
       nx * ny * nz > ((int64_t)1 << 34) || ny * nz > ((int64_t)1 << 31) ||
@@ -1310,7 +1307,8 @@ tdt_status_t tdt_poisson3d_create(int64_t nx, int64_t ny, int64_t nz, double hx,
     return (int64_t)(5 * tdt::kStrB) * ld * ny * 8 + 512 < ((int64_t)1 << 31);
   };
   // unpadded rows on the hipFFT path where padded ones are out of its reach
-  if (p->any && !p->closed && !lines_fit(padded_row(nx))) p->any = false;
+  if (p->any && !p->closed && !(pad && lines_fit(padded_row(nx)))) p->any = false;
+  *padded = p->any && !p->closed;
   // tables of every half-step: classes k < K_j with t_+-1 = -1,
   // t_0 = 2 + h^2 (w_kj + mu_k / 2), and the epilogue of the step
   std::vector<double> tab;
@@ -1420,6 +1418,25 @@ tdt_status_t tdt_poisson3d_create(int64_t nx, int64_t ny, int64_t nz, double hx,
   }
   *out = p;
   return TDT_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+tdt_status_t tdt_poisson3d_create(int64_t nx, int64_t ny, int64_t nz, double hx, double hy,
+                                  double hz, double eps, tdt_poisson3d_t* out) {
+  if (!out) return TDT_ERR_INVALID_ARG;
+  *out = nullptr;
+  bool padded = false;
+  tdt_status_t st = make_poisson3d(nx, ny, nz, hx, hy, hz, eps, true, &padded, out);
+  if (st == TDT_ERR_OOM && padded) {
+    // short rows' padding takes many times the memory of unpadded ones (Nx = 1:
+    // 64 doubles per row against 5)
+    (void)hipGetLastError();
+    st = make_poisson3d(nx, ny, nz, hx, hy, hz, eps, false, &padded, out);
+  }
+  return st;
 }
 
 tdt_status_t tdt_poisson3d_solve(tdt_poisson3d_t p, const double* F, double* U,
