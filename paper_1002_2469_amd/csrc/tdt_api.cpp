@@ -1511,12 +1511,19 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     // right-hand sides of 123 tiles in double: R = 6, final pass 46 us, R = 2,
     // 50 us; 300 of 10 tiles 45 against 52 us; but 30 of 39 tiles, three
     // quarters busy, 27 against 25 us for the whole solve).
+    // Not on float plans with a ragged last tile, whose first pass sweeps, with
+    // more than 64 tiles of a number that is no multiple of 4: a tile's groups
+    // then lie on different XCDs, whose L2s do not share its constants (16
+    // right-hand sides of 123 tiles 38 and 33 us, 7 of 250 36 and 32; but 12
+    // of 124 24 and 32, 48 of 30 23 and 26).
+    const bool one_round =
+        p->dtype != TDT_F32 || p->N % p->L == 0 || nt <= 64 || nt % 4 == 0;
     const int64_t slots_g = std::max(1, tdt::general_slots(p->dtype == TDT_F32 ? 1 : 0));
     auto items_of = [&](int r) { return nt * ((M + r - 1) / r); };
     const int rmax = (int)std::min<int64_t>(M, 8);
     int R = rmax;
     while (R > 1 && items_of(R) < 4 * (int64_t)tdt::device_cus()) --R;
-    for (int r = rmax; r >= 1; --r)   // (the fewest that do: even groups)
+    for (int r = one_round ? rmax : 0; r >= 1; --r)   // (the fewest that do: even groups)
       if (items_of(r) <= slots_g && 10 * items_of(r) >= 9 * slots_g) R = r;
     L.gen_R = R;
     const int64_t groups = (M + R - 1) / R;
