@@ -675,9 +675,10 @@ hipError_t launch_strided_tiled(StridedArgs a, const StridedTiles& g, const doub
   if (e != hipSuccess) return e;
   // Every workgroup of pass 2 eliminates its systems' interface values itself
   // where that costs less than a launch: few tiles, and few rounds of
-  // workgroups that repeat it (4 x 2000 x 1023, 4 tiles: one launch of 5 us
-  // less; 8191 x 8192, 16 tiles: pass 2 took 262 us with it, 220 us and a
-  // launch of 14 us without).
+  // workgroups that repeat it.  us with it and with the launch, by workgroups
+  // x tiles (rows of 1000 or 1024): 1000 20/24, 4000 26/31 (8 tiles), 16000
+  // 48/52 (16 tiles), 148/148 (4), 20000 111/110 (8), 33000 85/88 (16), 39000
+  // 352/345 (4), 179/176 (8), 131000 262/234 (16 tiles of 8191 x 8192).
   const int64_t cols = (a.M + kStrGroup - 1) / kStrGroup * g.K * a.nb;
   a.ends = g.K <= kStrInlineTiles && !a.epi && cols * g.K <= kStrInlineWork ? ends : nullptr;
   if (!a.ends) {
