@@ -44,6 +44,7 @@ every GPU result.
 from __future__ import annotations
 
 import argparse
+import ctypes
 import hashlib
 import json
 import os
@@ -159,8 +160,8 @@ def load_workload(name: str, args):
                  desc=f"poisson3d: seven-point Poisson problem on {d['nx']}x{d['ny']}x{d['nz']} "
                       f"interior points of the unit cube, zero boundary, F~N(0,1) seed 0, "
                       f"[Nz][Ny][Nx] double in/out; sine transform along x (fused row transform), "
-                      f"Peaceman-Rachford ADI per mode plane (optimal parameters, eps 1e-13, "
-                      f"strided line solves along y and z), inverse transform")
+                      f"Peaceman-Rachford ADI iterate per mode plane (optimal parameters, eps "
+                      f"1e-13) in closed form (sine transforms along y and z), inverse transform")
     elif name == "diff":
         d = W.diff_batch(seed=0)
         d.update(kind="varlen", units=int(d["offsets"][-1]), adjoint=True,
@@ -201,6 +202,22 @@ def plan_create_ms(tdt, d, mode, reps=3):
         times.append((time.perf_counter() - t0) * 1e3)
         p.close()
     return statistics.median(times)
+
+
+def count_launches(fn, torch):
+    """Kernel launches of fn(): the nodes of its captured graph (0: not known)."""
+    n = ctypes.c_size_t(0)
+    try:
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            fn()
+        with open("/proc/self/maps") as f:
+            path = next(line.split()[-1] for line in f if "libamdhip64.so" in line)
+        status = ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None,
+                                                    ctypes.byref(n))
+    except (OSError, RuntimeError, StopIteration):
+        return 0
+    return n.value if status == 0 else 0
 
 
 def run_mode(tdt, d, F, X, mode, steps, warmup, torch, opts=None):
@@ -258,6 +275,10 @@ def run_mode(tdt, d, F, X, mode, steps, warmup, torch, opts=None):
         kern[pre + "interface"] = prof["interface_ms"] / n
         kern[pre + "final_pass"] = prof["final_ms"] / n
     info = plan.info()
+    launches = {"fwd": count_launches(lambda: plan.solve(F, X), torch)}
+    if adj:   # (the reduction of the t-gradients is one more)
+        launches["bwd"] = count_launches(lambda: plan.backward(gX, X, gF, gt), torch) - 1
+    torch.cuda.synchronize()
 
     # step time: eager, or replays of a captured graph
     graph = None
@@ -289,7 +310,7 @@ def run_mode(tdt, d, F, X, mode, steps, warmup, torch, opts=None):
     solves = warmup + 2 * steps + (1 + warmup if d.get("graph") else 0)
     out = dict(ms=ms, kernels_ms=kern, refine_iters=info["refine_iters"],
                X=X.cpu().numpy().reshape(-1), tuned=tuned, stage1_ms=stage1_ms,
-               green_support=support, solves=solves)
+               green_support=support, solves=solves, launches=launches)
     if adj:
         out["gF"] = gF.cpu().numpy().reshape(-1)
         out["gt"] = gt.cpu().numpy()
@@ -332,7 +353,7 @@ def run_poisson(tdt, d, F, mode, steps, warmup, torch):
 
 
 def run_poisson3d(tdt, d, F, steps, warmup, torch):
-    """A step is one whole 3D solve (transforms and all ADI half-steps)."""
+    """A step is one whole 3D solve (transforms and the ADI iterate)."""
     t0 = time.perf_counter()
     solver = tdt.Poisson3D(d["nx"], d["ny"], d["nz"], d["hx"], d["hy"], d["hz"], d["eps"])
     stage1_ms = (time.perf_counter() - t0) * 1e3
@@ -564,12 +585,19 @@ def main() -> int:
         nmax = d["N"] if d["kind"] == "series" else max(b - a for a, b in zip(o, o[1:]))
         inline_itf = tile < nmax <= 64 * tile
     itf = ", interface pass inline" if inline_itf else ""
-    # a series with short supports is solved by the final pass alone, which
-    # forms the values outside its tiles from the supports' rows (the rows of
-    # its neighbours, read from cache, are not counted)
-    if d["kind"] == "series" and 0 < kf + kl <= 256 and n_first > 0:
-        per_launch["first_pass"] = 0.0
-        itf = ", outside values from the supports inline: one launch"
+    # one launch: the final pass forms the values outside its tiles from the
+    # rows of the supports (its neighbours' rows, read from cache, are not
+    # counted), or no system has more than one tile
+    itf_bwd = itf
+    if n_first > 0 and d["kind"] in ("series", "varlen"):
+        one = ", outside values from the supports inline: one launch"
+        launches = res[head]["launches"]
+        if launches["fwd"] == 1:
+            per_launch["first_pass"] = 0.0
+            itf = one
+        if launches.get("bwd") == 1:
+            per_launch["bwd_first_pass"] = 0.0
+            itf_bwd = one
     names = {"first_pass": (f"k_beta_ends<double> (tile summaries from the Green rows' "
                             f"supports, {kf} + {kl} rows per tile)" if kf + kl > 0 else
                             "k_beta<double> (Green-row tile summaries, first pass)"
@@ -590,7 +618,7 @@ def main() -> int:
              "adi": "k_dst_columns (the ADI iterates in closed form: sine transforms along "
                     "y, along z with the factor and back, back along y; summed)",
              "bwd_first_pass": "k_tile<double, *, SUMMARY> on T^T (adjoint first pass)",
-             "bwd_final_pass": f"k_tile<..., BWD> (adjoint solve, store gF, dL/dt partial sums{itf})"}
+             "bwd_final_pass": f"k_tile<..., BWD> (adjoint solve, store gF, dL/dt partial sums{itf_bwd})"}
 
     cpu = None
     errs = {}
