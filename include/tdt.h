@@ -35,10 +35,10 @@ typedef struct tdt_plan_s *tdt_plan_t;
  *   TDT_F32        every step in float (accuracy ~ cond(T) * 2^-24);
  *   TDT_F32_REFINE each tile's sweeps, its in-tile interface and the
  *                  correction in float; the tile summaries, the interface
- *                  pass across tiles, the residual r = F - T X and the
- *                  update X += d in double, repeated until the update stops
- *                  shrinking (iterative refinement), so the result matches
- *                  the double solve. */
+ *                  pass across tiles (corner rows included), the residual
+ *                  r = F - T X and the update X += d in double, repeated
+ *                  until the update stops shrinking (iterative refinement),
+ *                  so the result matches the double solve. */
 typedef enum { TDT_F64 = 0, TDT_F32 = 1, TDT_F32_REFINE = 2 } tdt_dtype_t;
 
 typedef enum {
@@ -272,7 +272,7 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p);
  * (lines of more than 1024 points are solved in tiles of 512, as by
  * tdt_solve_strided), 640 Nxp Ny < 2^31 with Nxp = 16 ceil(Nx/16) + 16 where
  * Nx+1 is a power of two from 128 to 8192, Nx otherwise (31-bit byte offsets
- * of the z lines),
+ * of the z lines, where they are iterated; the same bound for every handle),
  * 0 < eps < 1; a count above 400 for some mode -> TDT_ERR_INVALID_ARG.  The
  * handle owns the per-iteration tables (~(38 + 4 ceil(N/16)) doubles per
  * mode and iteration, about twice that for tiled lines), for tiled lines
@@ -450,9 +450,13 @@ tdt_status_t tdt_segment_merge(const double *l, const double *r, double *out);
  * interface pass itself, and the interface group is empty (two events with
  * nothing between them).  Where the Green rows of every multi-tile system
  * have short supports (tdt_green_support; a ragged last tile at least as long
- * as they need) the final pass forms the values outside its tiles from the
- * rows next to their ends, and the first-pass group is empty too: the solve
- * is one launch.  So are series of short systems, which share workgroups.
+ * as they need) and it expects that to pay for their lengths, the number of
+ * tiles and the dtype, the final pass forms the values outside its tiles from
+ * the rows next to their ends, and the first-pass group is empty too: the
+ * solve is one launch.  (A float series of fewer than four tiles, the last one
+ * ragged, and a varlen batch with one multi-tile system that does not qualify
+ * always keep the first pass.)  Series of short systems that share workgroups
+ * are one launch as well.
  * tdt_plan_profile_read synchronises the device, returns in ms3[0..2] the
  * summed milliseconds of the three groups over the recorded solves and in
  * *nsolves their number, and clears the record.  Disabling clears it too. */
@@ -471,11 +475,13 @@ tdt_status_t tdt_plan_profile_read(tdt_plan_t plan, double *ms3, int64_t *nsolve
  *       system through the tile-parallel path.  Without effect on batches
  *       that are one launch anyway (short supports throughout, see
  *       tdt_plan_profile), and on systems of at most 1024 rows where they are
- *       all of the batch or many of it (a wavefront each).
+ *       all of the batch or many of it (a wavefront each; not quasi-Toeplitz
+ *       ones of TDT_F32).
  *   TDT_OPT_WG_PER_CU        0 (default): the tile kernels launch one
  *       workgroup per tile and the other kernels as many workgroups as fit
  *       at once; k > 0: every kernel runs at most k persistent workgroups
- *       per compute unit, each looping over its share of the work.
+ *       per compute unit, each looping over its share of the work (as many
+ *       lanes in the narrower workgroups of short systems).
  *   TDT_OPT_MAX_REFINE       TDT_F32_REFINE: most float solves per tile
  *       (1..100, default 40).
  *   TDT_OPT_SHAPE            work shape of the tile kernels: 0 = blocks of

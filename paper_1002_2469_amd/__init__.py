@@ -407,9 +407,9 @@ class Poisson2D:
     """2D Poisson solve by separation of variables (Sec. 3.2): the five-point
     system on Nx x Ny interior points with zero boundary values, F and U
     [Ny][Nx] float64 on the device.  Sine transforms along x (one fused
-    kernel when Nx + 1 is at most 8192 with prime factors at most 13, hipFFT
-    otherwise), one Toeplitz line system per mode along y (in float64 with
-    the fused transform, mostly a strided plan solving the modes in place in
+    kernel when Nx + 1 is at most 8192 with prime factors at most 13, or at
+    most 512, a matrix product; hipFFT otherwise), one Toeplitz line system
+    per mode along y (in float64 with a fused transform, mostly a strided plan solving the modes in place in
     the transformed rows; otherwise a varlen plan of dtype 'f64' or
     'f32_refine' after a transpose), inverse transform."""
 
@@ -492,8 +492,8 @@ class Poisson3D:
     on the device.  Sine transform along x, Peaceman-Rachford ADI on every
     mode's (y, z) plane with the optimal parameters (strided line solves
     along y and z, or the same iterate in closed form through sine transforms
-    along y and z where Ny + 1 and Nz + 1 are at most 512 or, up to 1024, have small factors), inverse
-    transform.  eps bounds the ADI error
+    along y and z where Ny + 1 and Nz + 1 are at most 512 or, up to 1024, have
+    prime factors of at most 13), inverse transform.  eps bounds the ADI error
     relative to the exact discrete solution (2-norm)."""
 
     def __init__(self, nx: int, ny: int, nz: int, hx: float, hy: float, hz: float,

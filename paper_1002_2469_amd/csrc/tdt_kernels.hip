@@ -473,10 +473,6 @@ __device__ __forceinline__ void inline_ghosts(const SysDesc& S, int t, double u,
   XR = __shfl(un, t, 64);
 }
 
-// One wavefront's dot product of k rows of a tile with k entries of a Green
-// row's support (k a multiple of 64; both pointers already offset by the
-// lane), U rows in flight per lane.  The lane sums are added by a fixed
-// butterfly, so the result is repeatable and the same in every lane.
 // Both ends of a tile in one wavefront: H rows of the head and H of the tail
 // in flight together per lane (for short supports, where a wavefront per end
 // would cost more to launch than it saves in waiting).
@@ -509,6 +505,10 @@ __device__ __forceinline__ void support_dot2(const Tio* head, const double* gf, 
   }
 }
 
+// One wavefront's dot product of k rows of a tile with k entries of a Green
+// row's support (k a multiple of 64; both pointers already offset by the
+// lane), U rows in flight per lane.  The lane sums are added by a fixed
+// butterfly, so the result is repeatable and the same in every lane.
 template <typename Tio, int U>
 __device__ __forceinline__ double support_dot(const Tio* rows, const double* g, int k) {
   const int nr = k / 64;
