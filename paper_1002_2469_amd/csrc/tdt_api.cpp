@@ -867,7 +867,13 @@ bool corner_table(const SysDesc& D, int NT, double* t64) {
 // a launch of their own, about 5 us; in the other kernels a short system costs
 // about 14 ns of the whole device at 512 lanes and 5 ns at 256 (the 512 short
 // ones of the 2048-system separation-of-variables batch: 94.5 us together
-// with the others, 99.6 us in a launch of their own).
+// with the others, 99.6 us in a launch of their own).  A refined batch of
+// short systems alone takes the path once the whole-system kernel's workgroups
+// would fill half of the device (256 lanes: three quarters); below, that
+// kernel is the faster one (200 systems of 250 to 1000 rows, quasi-Toeplitz in
+// brackets: 256 lanes 9.5 and 11.8 us (10.2 and 13.5), 512 lanes 11.7 and 11.8
+// (13.0 and 14.5); 700 of them 12.7 and 13.0 (14.5 and 15.7), 23.2 and 13.0
+// (27.6 and 15.7)).
 tdt_status_t mark_short(tdt_plan_s* p, int dir) {
   const size_t S = p->hsys[dir].size();
   std::vector<char>& ok = p->short_ok[dir];
@@ -882,7 +888,10 @@ tdt_status_t mark_short(tdt_plan_s* p, int dir) {
             (!p->varlen || p->in_sizes[s] <= (int64_t)tdt::kShortItemNT * tdt::kShortB);
     count += ok[s];
   }
-  if (count == 0 || (count < S && count < 4 * (size_t)tdt::device_cus())) {
+  const size_t cus = (size_t)tdt::device_cus();
+  const bool few = p->varlen && p->dtype == TDT_F32_REFINE &&
+                   4 * count * p->NT <= (p->NT > 256 ? 2 : 3) * cus * 1024;
+  if (count == 0 || (count < S && count < 4 * cus) || few) {
     ok.assign(S, 0);
     return TDT_OK;
   }
