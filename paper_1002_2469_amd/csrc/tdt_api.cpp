@@ -694,11 +694,17 @@ void destroy(tdt_plan_s* p) {
 // lanes 13.3/11.2, 600 14.7/16.7, 2048 31/39; of 256 lanes 1088 13.6/11.6,
 // 1296 14.3/16.2), three where a ragged last tile would be swept in a launch
 // of its own (30011 rows: 1496 tiles of 512 lanes 24.5/22.5, 1900 33.9/37.3).
+// A batch of systems of one tile each (single; quasi-Toeplitz) is one launch of
+// the whole-system kernel otherwise, in float forward the faster one past a
+// round of workgroups (systems of 750 to 3000 rows, 512 lanes: 400 8.7/8.2, 700
+// 10.3/12.2, the adjoint 27.1/22.3; 256 lanes: 1000 9.0/8.7, 1500 10.6/12.5).
 // Refined quasi-Toeplitz systems in blocks of 8 rows, whose kernel is short of
 // registers, forward: 2048 tiles 48/45, 4096 77/85 (64 + 64 to 192 + 192).
-bool halo_pays(const tdt_plan_s* p, int dir, int64_t rows, int64_t tiles, bool ragged) {
+bool halo_pays(const tdt_plan_s* p, int dir, int64_t rows, int64_t tiles, bool ragged,
+               bool single) {
   if (p->dtype == TDT_F32) {
     const int64_t round = (int64_t)tdt::device_cus() * 1024 / p->NT;
+    if (single && dir == 0 && tiles > round) return false;
     return rows <= 256 || tiles <= 256 ||
            (rows <= 512 && tiles <= std::min<int64_t>(ragged ? 3 * round : round + round / 16, 2048));
   }
@@ -993,17 +999,18 @@ tdt_status_t finish_plan(tdt_plan_s* p, const std::vector<double>& tm1,
       // launch is there anyway, and the others do better in it:
       // separation-of-variables batch 94.5 us, 98 with them in the final pass
       // alone; 1000 quasi-Toeplitz systems with refinement 149 and 182.
-      bool all = true, ragged = false;
+      bool all = true, ragged = false, single = true;
       int64_t rows = 0, tiles = 0;
       for (int64_t s = 0; s < S; ++s) {
         const SysDesc& D = p->hsys[dir][s];
         if (p->short_ok[dir][s]) continue;
         tiles += D.ntiles;
         ragged = ragged || D.n % kTile != 0;
+        single = single && D.ntiles == 1;
         rows = std::max<int64_t>(rows, D.gkf + D.gkl);
         if (needs_interface(D) && !D.halo) all = false;
       }
-      if (!all || !halo_pays(p, dir, rows, tiles, ragged))
+      if (!all || !halo_pays(p, dir, rows, tiles, ragged, single))
         for (SysDesc& D : p->hsys[dir]) D.halo = 0;
       (void)hipFree(p->dgpack[dir]);
       p->dgpack[dir] = nullptr;
@@ -1578,7 +1585,7 @@ tdt_status_t launch_set(tdt_plan_s* p, int dir, bool adjoint, int64_t M, tdt::La
     const bool itf =
         need && !(p->hsys[dir][0].halo && !sweep &&
                   halo_pays(p, dir, p->green_kf[dir] + p->green_kl[dir], M * nt,
-                            D0.n % p->L != 0));
+                            D0.n % p->L != 0, false));
     L.halo = need && !itf ? 1 : 0;
     L.p1_items = nullptr;
     L.fin_items = nullptr;

@@ -1,7 +1,8 @@
 """GPU parity of varlen batches on both sides of the lines between the
 whole-system kernel and the paths that replace it: refined batches of short
 systems (256 workgroups of 512 lanes, 768 of 256 are half and three quarters of
-the device), forward and adjoint, the gradients by component.
+the device), float batches of one-tile quasi-Toeplitz systems (one round of
+workgroups); forward and adjoint, the gradients by component.
 
 Tolerances: X and gF those of the other short-system tests.  A gradient is a
 sum of products of the device's own gF and X, formed in double in a tree of at
@@ -20,11 +21,11 @@ from test_gpu_short_routes import gradient_and_mass
 pytestmark = pytest.mark.gpu
 
 
-def _check_batch(sizes, dtype, quasi, shape):
+def _check_batch(sizes, dtype, quasi, shape, ratio=1.25):
     import paper_1002_2469_amd as tdt
     rng = np.random.default_rng(len(sizes))
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
-    t = np.array([quasi_system(rng, 1.25) for _ in sizes]).T
+    t = np.array([quasi_system(rng, ratio) for _ in sizes]).T
     q = dict(psi=t[3], chi=t[4]) if quasi else {}
     F, W = rng.standard_normal((2, off[-1]))
     if dtype == "f32":
@@ -56,3 +57,15 @@ def test_refined_short_batches(quasi, shape, S):
     sizes = np.random.default_rng(S).integers(3, 1025, S)
     sizes[0] = 1024
     _check_batch(sizes, "f32_refine", quasi, shape)
+
+
+@pytest.mark.parametrize("shape,S", [(0, 512), (0, 513), (2, 1024), (2, 1025)])
+@pytest.mark.parametrize("ratio", [1.25, 1.9])
+def test_float_one_tile_batches(ratio, shape, S):
+    """Quasi-Toeplitz systems of one tile, longer than the short ones: up to a
+    round of workgroups (512 of 512 lanes, 1024 of 256) forward by the tile
+    kernel, above by the whole-system kernel; the adjoint by the tile kernel."""
+    print(f"[case] float one-tile batch S={S} shape={shape} ratio={ratio}", flush=True)
+    sizes = np.random.default_rng(S).integers(1025, (8192 if shape == 0 else 4096) + 1, S)
+    sizes[0] = 8194 if shape == 0 else 4098
+    _check_batch(sizes, "f32", True, shape, ratio)
