@@ -11,7 +11,7 @@
 // Z_{n-k}) / 2, Y^B_k = (Z_k - conj Z_{n-k}) / 2i, S_2k = -Im Y_k, and the odd
 // coefficients are the prefix sums of Re Y_k.  One pass over HBM, where a
 // library FFT between separate fold, split and prefix-sum kernels takes four:
-// the 2D solve of 999 x 1499 points 89 -> 45 us, of 4094 x 4000 1437 -> 276 us (with the
+// the 2D solve of 999 x 1499 points 86 -> 42 us, of 4094 x 4000 1434 -> 257 us (with the
 // in-place line solves it allows).
 //
 // Bound by HBM on large arrays (columns of 511 entries: 445 us for 2.15 GB,

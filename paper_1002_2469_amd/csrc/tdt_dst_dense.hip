@@ -15,8 +15,8 @@
 // (50 x 100000 points, 80 MB, 44 us), by launches when small.  Before, a
 // library FFT between fold, split and prefix-sum kernels, transposes around
 // the 2D line solves and the iterated 3D half-steps: 2D 50 x 1000 points 42 ->
-// 20 us, 250 x 20000 378 -> 148, 508 x 60000 2280 -> 1118; 3D 40 x 50 x 59 604 ->
-// 29, 100^3 781 -> 61, 300^3 6905 -> 1448.  Above 512 the matrix outgrows both the
+// 20 us, 250 x 20000 360 -> 140, 508 x 60000 2263 -> 1088; 3D 40 x 50 x 59 602 ->
+// 28, 100^3 781 -> 55, 300^3 6926 -> 1286.  Above 512 the matrix outgrows both the
 // work saved and the LDS.  Where there are at least two workgroups per compute
 // unit, 32 sequences share each load of the matrix (CT = 2); below, 16 (more
 // workgroups), and a few rows' tiles are dealt to several workgroups (508 x 500

@@ -18,8 +18,8 @@
 //     S_{2k} = -Im Y_k,   S_1 = Re Y_0 / 2,   S_{2k+1} = S_{2k-1} + Re Y_k,
 // the odd coefficients a prefix sum along k.  One kernel does all of it where
 // Nx + 1 is a power of two (k_dst_rows), has small factors (tdt_dst.hip) or is
-// at most 512 (tdt_dst_dense.hip); otherwise the FFTs are hipFFT's between this library's fold and prefix-sum
-// kernels.
+// at most 512 (tdt_dst_dense.hip); otherwise the FFTs are hipFFT's between this
+// library's fold and prefix-sum kernels.
 #include <hip/hip_runtime.h>
 #include <hipfft/hipfft.h>
 #include <stdint.h>
@@ -791,8 +791,8 @@ tdt_status_t tdt_poisson2d_create(int64_t nx, int64_t ny, double hx, double hy,
   // in place in the transformed rows, as a strided batch (system k: column
   // k), with padded rows.  Otherwise transposes to and from mode-major order
   // around a varlen plan (also for short rows, whose padding would outweigh
-  // them).  Measured in place and transposed: 199 x 3000 38.8 and 43.5 us,
-  // 999 x 1499 45 and 61, 4094 x 4000 276 and 402.
+  // them).  Measured in place and transposed: 199 x 3000 35 and 39 us,
+  // 999 x 1499 46 and 58, 4094 x 4000 257 and 386.
   p->strided = dtype == TDT_F64 &&
                (p->fused || (p->any && nx >= 64 && ny <= tdt::kStrMaxN));
   p->ldw = p->strided ? padded_row(nx) : n;
@@ -1035,7 +1035,7 @@ tdt_status_t tdt_poisson2d_destroy(tdt_poisson_t p) {
 // transforms take Ny + 1 and Nz + 1 (tdt_dst.h) the iterate is formed from that (closed_solve):
 // three passes over the array (transform along y; along z, the factor, and
 // back; back along y), 48 bytes per unknown, instead of 40 per iteration and
-// about 12 iterations: 511^3 14.65 -> 2.51 ms, error against the exact
+// about 12 iterations: 511^3 14.68 -> 2.49 ms, error against the exact
 // solution 4e-13 -> 5e-14.  (Chunks of modes small enough for the Infinity
 // Cache did not help the iteration: 14.2 ms at best, its half-steps being as
 // slow from cache.)

@@ -116,8 +116,8 @@ __device__ __forceinline__ void interface_inline(const StridedArgs& a, int64_t b
 
 // Pass 1 of a group whose Green rows have short supports (bound by latency; it
 // reads kf + kl of 512 rows: the whole pass on the 8191 x 8192 modes of a
-// Poisson problem, 93 % of whose groups take it, 135 -> 47 us; 4 x 2000 x 1023
-// 31 -> 15 us with the last tiles in the same launch): the first unknown
+// Poisson problem, 93 % of whose groups take it, 135 -> 46 us; 4 x 2000 x 1023
+// 31 -> 13 us with the last tiles in the same launch): the first unknown
 // of a tile is sum_j f_j rf^j / u* over its first kf rows, the last one the
 // same over its last kl rows from the end, rf = -t_1 / u*, rl = -t_-1 / u*
 // (the rows of eq. (9) under dominance, Sec. 3.4, all but 2^-60 of their
@@ -693,8 +693,8 @@ hipError_t launch_strided(const StridedArgs& a0, hipStream_t st) {
   StridedArgs a = a0;
   // Rows that do not start on a cache line: neighbouring groups share lines,
   // so they go to one XCD, whose L2 then reads such a line once and merges
-  // the two stores to it (4 x 2000 x 1023: 61.6 -> 45.9 us).  On aligned rows
-  // the hardware's order is the better one (8191 x 8192: 294 against 322 us),
+  // the two stores to it (4 x 2000 x 1023: 56.5 -> 41.8 us).  On aligned rows
+  // the hardware's order is the better one (8191 x 8192: 277 against 306 us),
   // and for the ADI half-steps on unaligned ones (3 %).
   const bool aligned = (reinterpret_cast<uintptr_t>(a.R) | reinterpret_cast<uintptr_t>(a.O)) %
                                128 == 0 && a.ld % 16 == 0 && a.ldb % 16 == 0;
